@@ -116,6 +116,11 @@ void mf_footprint_destroy(mf_footprint* fp);
  * around (x, y).  img/out: device pointers, stride_bytes as above; dtype is
  * an mf_dtype and boundary an mf_boundary.
  *
+ * Windows of up to a few hundred taps (more on small images) are selected
+ * on bit planes, the others by the tile engine; which path runs is an
+ * estimate from window, type and image size and never changes a result.  A
+ * tile override or enabled work counters send every call to the tile engine.
+ *
  * Memory: the first call with a footprint on a device uploads its span
  * table (kept until mf_footprint_destroy).  Large windows (global-scratch
  * tiles) use a scratch buffer cached per (device, stream), allocated on first
@@ -368,7 +373,8 @@ int mf_release_scratch(void);
  * groups tested, [7] box pixels ranked by the ordinal transforms, [8]
  * shader clocks in seed solves (part of [3]), [9] shader clocks from tile start
  * to the box loaded (part of [2]; 0 for global-scratch tiles).  The
- * learned and bracketed filters count into the same counters.  enable = 0:
+ * learned and bracketed filters count into the same counters; while they
+ * are enabled every plain call runs the tile engine.  enable = 0:
  * stop counting and free them.  enable = -1: copy the ten counters to the
  * host array `out10` (synchronous).  Not thread-safe against concurrent
  * filter calls.  Counting adds a few scalar instructions per block. */
@@ -408,9 +414,10 @@ int mf_plan_autotune(const mf_image_desc* descs, int n, hipStream_t stream, int 
 int mf_tune_cache_load(const char* path);
 int mf_tune_cache_save(const char* path);
 
-/* The tile shape and launch the plain filter would use for this image and
- * footprint: output tile size, input box size (tile + window extent) and
- * the LDS bytes per workgroup.  Host-only; runs no GPU code. */
+/* The tile shape and launch of the tile engine for this image and footprint
+ * (calls that run on bit planes instead have a tile of their own): output
+ * tile size, input box size (tile + window extent) and the LDS bytes per
+ * workgroup.  Host-only; runs no GPU code. */
 int mf_query_plan(int w, int h, int dtype, const mf_footprint* fp, int* tile_w, int* tile_h,
                   int* box_w, int* box_h, int* lds_bytes);
 

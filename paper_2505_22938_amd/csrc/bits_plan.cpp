@@ -1,0 +1,130 @@
+// Host side of the bit-plane path (bitplane.h): which windows take it, which
+// variant, and the launch.
+
+#include <algorithm>
+
+#include "mf_internal.h"
+
+namespace mf {
+
+namespace {
+
+struct Variant {
+  int g, p, threads, sx, sy, tw, th;
+};
+
+template <int G, int P>
+constexpr Variant variant() {
+  using B = BitsGeo<G>;
+  return {G, P, B::NT, B::SX, B::SY, B::TW, B::TH};
+}
+
+constexpr Variant kVariants[] = {
+#define MF_BITS_ROW(I, G, P) variant<G, P>(),
+    MF_BITS_VARIANTS(MF_BITS_ROW)
+#undef MF_BITS_ROW
+};
+static_assert(sizeof(kVariants) / sizeof(kVariants[0]) == kBitsVariants, "variant table");
+
+// LDS: eight planes of the words, the box, the tap table
+int lds_bytes(const Variant& v, int W, int H, int es) {
+  const BitsLayout l = bits_layout(v.sx, v.sy, W, H);
+  return 32 * l.nw + es * l.rp * l.rh + 4 * v.g * v.p;
+}
+
+// Estimated time in microseconds of variant v on a w x h image: instructions
+// of a wave times the cycles each takes, plus launch, box load and output.
+// A SIMD issues one vector instruction in about nine cycles with one wave on
+// it and one in about four with two or more (measured with chains of single
+// instructions: 9.4 and 4.8, 4.5 with four waves); the largest boxes leave
+// room in the LDS for one workgroup, one wave per SIMD.  Estimated / measured
+// us: uint16 disc 1 / 5 / 8 / 12 at 4096 x 4096 45 / 132 / 396 / 957 against
+// 35 / 138 / 369 / 902; uint8 disc 4 / 16 at 256 x 256 15 / 23 against 10 / 17.
+double bits_us(const Variant& v, int W, int H, int es, int lds_max, long long w, long long h) {
+  const BitsLayout l = bits_layout(v.sx, v.sy, W, H);
+  int lg = 0;
+  while ((1 << lg) < v.g) ++lg;
+  const double build = 350.0 * ((l.nw / 4 + v.threads - 1) / v.threads) + 120.0;
+  const double n = es * (8.0 * (9.3 * v.p + 40.0 + 24.0 * lg) + build) + 600.0;
+  const double waves = (double)((w + v.tw - 1) / v.tw) * (double)((h + v.th - 1) / v.th) *
+                       (v.threads / 64);
+  const double cycles = 2 * lds_bytes(v, W, H, es) <= lds_max ? 4.2 : 9.0;
+  return 6.0 + std::max(9.0, cycles * waves / 1024.0) * n / 2400.0;
+}
+
+// The tile engine on the same image, near the line where the two paths meet:
+// per pixel as at 4096 x 4096 (disc 8 to 16: uint8 1.21 to 1.26 ms, uint16
+// 1.00 to 1.06, float32 1.35 to 1.50), and no less than the few tiles of a
+// small image take (256 x 256 to 641 x 479, disc 4 to 20: 75 to 180 us).  At
+// 4096 x 4096 the bit planes win up to disc 12 for uint16 (0.90 against 1.00
+// ms; disc 13 1.02 against 1.00), disc 17 for uint8 (disc 16 0.87 against
+// 1.26) and disc 10 for float32 (0.98 against 1.40; disc 12 1.8 against
+// 1.35), and by 2.9x / 6.3x / 2.1x at disc 8.
+double tile_us(int dtype, long long w, long long h) {
+  const double ns = dtype == MF_U8 ? 0.073 : dtype == MF_U16 ? 0.060 : 0.083;
+  return std::max(90.0, 1e-3 * ns * (double)w * (double)h);
+}
+
+}  // namespace
+
+int bits_threads(int v) { return kVariants[v].threads; }
+
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, ImageDesc* d) {
+  int tw = 0, th = 0;
+  get_override(&tw, &th);
+  // a tile shape asks for the tile engine, and the work counters count its work
+  if (tw > 0 || work_counters_ptr()) return MF_ERR_UNSUPPORTED;
+  const int H = (int)fp->row_lo.size(), W = (int)fp->col_lo.size(), es = elem_size(dtype);
+  if (H > 64) return MF_ERR_UNSUPPORTED;   // the tap table is built by one wave, a row per lane
+  int pairs = 0;
+  for (int i = 0; i < H; ++i) {
+    if (fp->row_hi[i] < fp->row_lo[i]) return MF_ERR_UNSUPPORTED;
+    pairs += (fp->row_hi[i] - fp->row_lo[i] + 2) / 2;
+  }
+  int best = -1;
+  double best_us = tile_us(dtype, w, h);
+  for (int i = 0; i < kBitsVariants; ++i) {
+    const Variant& v = kVariants[i];
+    if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
+    const double us = bits_us(v, W, H, es, lds_max, w, h);
+    if (us < best_us) {
+      best = i;
+      best_us = us;
+    }
+  }
+  if (best < 0) return MF_ERR_UNSUPPORTED;
+  const Variant& v = kVariants[best];
+  *d = ImageDesc{};
+  d->bits = 1 + best;
+  d->kt = dtype;
+  d->shape = fp->kind == 0 ? SHAPE_DISC : SHAPE_SPANS;
+  d->tw = v.tw;
+  d->th = v.th;
+  d->bw = v.tw + W - 1;
+  d->bh = v.th + H - 1;
+  d->T = d->bw * d->bh;
+  d->dx_min = fp->dx_min;
+  d->dy_min = fp->dy_min;
+  d->nrows = H;
+  d->ncols = W;
+  d->limit = (int)fp->limit;
+  d->lds_bytes = lds_bytes(v, W, H, es);
+  return MF_OK;
+}
+
+int launch_bits(const ImageDesc& a, hipStream_t stream) {
+  const int v = a.bits - 1;
+  PlainKernelFn k = a.kt == MF_U8 ? pick_bits_u8(v) : a.kt == MF_U16 ? pick_bits_u16(v)
+                                                                     : pick_bits_f32(v);
+  const long long ntiles = (long long)a.tiles_x * a.tiles_y;
+  if (ntiles > 0x7fffffffLL) return MF_ERR_UNSUPPORTED;
+  (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            a.lds_bytes);
+  void* args[] = {const_cast<ImageDesc*>(&a)};
+  if (hipLaunchKernel((const void*)k, dim3((unsigned)ntiles), dim3((unsigned)bits_threads(v)), args,
+                      (size_t)a.lds_bytes, stream) != hipSuccess)
+    return MF_ERR_HIP;
+  return MF_OK;
+}
+
+}  // namespace mf

@@ -79,7 +79,9 @@ extern "C" int median_filter_noalloc(const void* img, int w, int h, size_t strid
   if ((rc = scratch_ptr(dev, &base))) return rc;
 
   ImageDesc a{};
-  if ((rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus))) return rc;
+  if (bits_plan(dtype, fp, di.lds_max, w, h, &a) != MF_OK &&
+      (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
+    return rc;
   const size_t nspan = footprint_span_table_len(fp) / 2;
   if (nspan > (size_t)kMaxSpans || nspan * sizeof(short2) > kSpanRegion)
     return MF_ERR_SCRATCH_LIMIT;
@@ -92,5 +94,6 @@ extern "C" int median_filter_noalloc(const void* img, int w, int h, size_t strid
 
   bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, (fp->taps - 1) / 2, table);
   a.out = out;
+  if (a.bits) return launch_bits(a, stream);
   return launch_with_plan(a, dev, di, stream, base + kSpanRegion, kSlotRegion);
 }

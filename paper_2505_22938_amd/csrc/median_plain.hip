@@ -162,11 +162,12 @@ int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
   rc = footprint_device_table(fp, dev, &table, stream);
   if (rc) return rc;
   ImageDesc a{};
-  rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus);
-  if (rc) return rc;
+  if (bits_plan(dtype, fp, di.lds_max, w, h, &a) != MF_OK &&
+      (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
+    return rc;
   bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, rank, table);
   a.out = out;
-  return launch_with_plan(a, dev, di, stream);
+  return a.bits ? launch_bits(a, stream) : launch_with_plan(a, dev, di, stream);
 }
 
 // Chained tiles (median_filter_chained): the plan of the footprint with an

@@ -41,6 +41,42 @@ constexpr int kHistBytes = kWaves * kHistWords * 4;
 enum { KEY_U8 = 0, KEY_U16 = 1, KEY_F32 = 2 };
 enum { SHAPE_DISC = 0, SHAPE_SPANS = 1 };
 
+// Bit-plane variants (bitplane.h): index, lanes per window, tap pairs per
+// lane.  A window of n pairs fits where n <= lanes * pairs.
+#define MF_BITS_VARIANTS(X) \
+  X(0, 1, 4) X(1, 1, 9) X(2, 1, 18) X(3, 1, 29) X(4, 1, 46) \
+  X(5, 2, 32) X(6, 2, 41) X(7, 2, 50) \
+  X(8, 4, 8) X(9, 4, 12) X(10, 4, 18) X(11, 4, 27) X(12, 4, 34) X(13, 4, 43) X(14, 4, 50) \
+  X(15, 8, 22) X(16, 8, 30) X(17, 8, 36) X(18, 8, 42) X(19, 8, 47) \
+  X(20, 16, 22) X(21, 16, 27) X(22, 16, 33) X(23, 16, 41) X(24, 16, 50)
+constexpr int kBitsVariants = 25;
+
+// Their workgroup and tile: G lanes share a window; GX x GY sub-tiles of SX x
+// SY pixels, one word of 32 pixels (one of each sub-tile) per G threads.
+template <int G>
+struct BitsGeo {
+  static constexpr int NT = 256;   // threads
+  static constexpr int WD = NT / G;               // words = pixels of a sub-tile
+  static constexpr int SX = G <= 2 ? 32 : G == 16 ? 8 : 16;
+  static constexpr int SY = WD / SX;
+  static constexpr int GX = 4, GY = 8;
+  static constexpr int TW = GX * SX, TH = GY * SY;
+};
+
+// LDS layout for a window of W x H: rows of `pitch` words (a multiple of
+// four), nw words a plane; box rows of rp pixels, rh of them.
+struct BitsLayout {
+  int pitch, nw, rp, rh;
+};
+__host__ __device__ inline BitsLayout bits_layout(int sx, int sy, int W, int H) {
+  BitsLayout l;
+  l.pitch = (sx + W - 1 + 3) & ~3;
+  l.nw = l.pitch * (sy + H - 1);
+  l.rp = (3 * sx + l.pitch + 15) & ~15;
+  l.rh = 8 * sy + H - 1;
+  return l;
+}
+
 // Everything one tile needs to know about its image and plan.  Passed by
 // value to the plain kernels and stored in the batched descriptor table.
 constexpr int kMaxRankOutputs = MF_MAX_RANK_OUTPUTS;   // planes of one general-rank call
@@ -77,6 +113,7 @@ struct ImageDesc {
   // kernel selection: key type, shape, 1 = global-scratch variant, and the
   // register capacity (elements per thread) of the LDS variant
   int kt, shape, gs, imax;
+  int bits;   // 0, or 1 + the bit-plane variant (tw x th then its tile)
   // bracketed tiles (learned path): per-tile [lo, hi] keys, the number of
   // in-bracket pixels region A can hold, and the list (y * w + x) and count
   // of output pixels whose median fell outside their tile's bracket
@@ -166,6 +203,14 @@ using PlainKernelFn = void (*)(ImageDesc);
 int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t stream,
                      unsigned char* ext_scratch = nullptr, size_t ext_bytes = 0);
 PlainKernelFn pick_general_kernel(const ImageDesc& d);
+// Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
+// kernel, and launch with a complete plan.
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, ImageDesc* d);
+PlainKernelFn pick_bits_u8(int v);
+PlainKernelFn pick_bits_u16(int v);
+PlainKernelFn pick_bits_f32(int v);
+int bits_threads(int v);
+int launch_bits(const ImageDesc& a, hipStream_t stream);
 // median_filter_windows: one pass for all windows (set by
 // mf_set_window_fusion) instead of grouping them by box size.
 bool window_fusion_all();
