@@ -89,6 +89,14 @@ __device__ __forceinline__ int dot2_sq_add(s2v d, int c) {
   return r;
 }
 
+// Window centre as the membership tests take it: x | y << 16, each a signed
+// 16-bit number (a window to the right of its centre puts the centres of a
+// tile's first columns left of the box; a disc's centre is always inside).
+template <int SHAPE>
+__device__ __forceinline__ uint32_t pack_centre(int cx, int cy) {
+  return (SHAPE == SHAPE_DISC ? (uint32_t)cx : (uint32_t)cx & 0xffffu) | ((uint32_t)cy << 16);
+}
+
 // Footprint geometry seen by the scans, walks and seed solves: the disc's
 // squared-radius limit, the first row offset and the row count (row spans
 // are in the LDS table rsp, index dy - dy_min).  One per output plane when
@@ -239,7 +247,7 @@ __device__ __forceinline__ int scan_select(int p, int c, int k, int cx, int cy, 
                                            const D& a, const Fp& f, const uint16_t* om,
                                            const short2* rsp, int& blocks, int& c_end) {
   const int lane = threadIdx.x & 63;
-  const uint32_t cxy = (uint32_t)cx | ((uint32_t)cy << 16);
+  const uint32_t cxy = pack_centre<SHAPE>(cx, cy);
   const bool up = c <= k;
   const uint32_t pre = up ? om[min(max(p + lane, 0), T - 1)] : om[max(p - 64 + lane, 0)];
   return scan_core<SHAPE, OM_LDS>(p, c, k, cxy, T, a, f, om, rsp, blocks, pre, pre, c_end);
@@ -1336,8 +1344,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
           }
           const int cnt = lc + wave_sum(d);
           int c_end = 0;
-          ms = wave_select<SHAPE>(lp, cnt, kseed, (uint32_t)(cx0 + 16) | ((uint32_t)cyg << 16),
-                                  Tv, f, om, rsp, groups, c_end);
+          ms = wave_select<SHAPE>(lp, cnt, kseed, pack_centre<SHAPE>(cx0 + 16, cyg), Tv, f, om, rsp, groups, c_end);
           sp = (!BR || ms >= 0) ? ms : (cnt <= kseed ? Tv : 1);
           sc = (!BR || ms >= 0) ? kseed : c_end;
         }
@@ -1377,7 +1384,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
         const int cnt = hc + row_sum16(d);
         int c_end = 0;
         const int ms = row_select<SHAPE>(act, hp, cnt, kc,
-                                         (uint32_t)(cxp + 1) | ((uint32_t)cy << 16), Tv, f, om,
+                                         pack_centre<SHAPE>(cxp + 1, cy), Tv, f, om,
                                          rsp, groups, c_end);
         if (act) {
           if (!BR || ms >= 0) {
@@ -1452,7 +1459,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
     }
     int pl = vp, cl = vc + delta;
     int mnew = m, esc = 0;
-    const uint32_t cxy = (uint32_t)cxl | ((uint32_t)(row0 + r - a.dy_min) << 16);
+    const uint32_t cxy = pack_centre<SHAPE>(cxl, row0 + r - a.dy_min);
     if (lane_active) {
       mnew = lane_select<SHAPE>(pl, cl, kl, cxy, kLaneBudget, Tv, f, om, rsp, groups);
       if (BR && mnew < 0 && (pl <= 0 || pl >= Tv)) {
