@@ -167,6 +167,90 @@ __device__ __forceinline__ uint32_t lds_load_early(const uint16_t* base, int i) 
   return *((lds_u16*)base + i);
 }
 
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
+}
+
+// Footprint rows i, i + RS, .. (N of them, those below nrows) against the
+// pivot p: entries entering minus entries leaving below it, their offsets
+// from hrow, relative to element `base` of the ordinal image.  All reads are
+// issued before the first compare, and signs are collected in masks (see
+// slide_count).
+template <int N, int RS>
+__device__ __forceinline__ int rows_below(const int2* hrow, const uint16_t* I, int nrows, int i,
+                                          int base, int p) {
+  int2 o[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) o[n] = hrow[N == 1 ? i : min(i + n * RS, nrows - 1)];
+  int e[N], l[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    e[n] = I[base + o[n].x];
+    l[n] = I[base + o[n].y];
+  }
+  int d = 0;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const int v = ((l[n] - p) >> 31) - ((e[n] - p) >> 31);
+    d += N == 1 || i + n * RS < nrows ? v : 0;
+  }
+  return d;
+}
+
+// Vertical slide of one lane's window: entering minus leaving entries of the
+// ordinal image below the pivot vp, over the window's columns.  vt: column
+// offsets (entering | leaving << 16, 16-bit elements), n8 of them padded
+// (none if 0: then ncols unpadded ones); lb: the LDS address they start
+// from.  Eight columns at a time: their sixteen entries are in flight
+// together and the next eight offsets behind them, so a lane waits for the
+// LDS once per eight columns; one dot product with (2, 0) or (0, 2) unpacks
+// an offset, scales it to bytes and adds the address.
+typedef unsigned short u2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int slide_count(const uint32_t* vt, int n8, int ncols, uint32_t lb,
+                                           int vp) {
+  using lds_u16 = const __attribute__((address_space(3))) uint16_t;
+  auto enter = [&](uint32_t o) -> int {
+    return *(lds_u16*)(size_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u2v, o), u2v{2, 0}, lb, false);
+  };
+  auto leave = [&](uint32_t o) -> int {
+    return *(lds_u16*)(size_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u2v, o), u2v{0, 2}, lb, false);
+  };
+  if (n8) {
+    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    using lds_u4 = const volatile __attribute__((address_space(3))) u4v;   // (read where written)
+    lds_u4* t4 = (lds_u4*)(size_t)lds_address(vt);
+    u4v ta = t4[0], tb = t4[1];
+    int ne = 0, nl = 0;
+    for (int j = 0; j < n8; j += 8) {
+      const uint32_t o[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
+      int e[8], l[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        e[i] = enter(o[i]);
+        l[i] = leave(o[i]);
+      }
+      const int nj = min(j + 8, n8 - 8) >> 2;
+      ta = t4[nj];
+      tb = t4[nj + 1];
+      // signs of entry - vp shifted into masks (no carry: a compare's result
+      // may only be added two issue slots later)
+      uint32_t me = 0, ml = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        me = __builtin_amdgcn_alignbit(me, (uint32_t)(e[i] - vp), 31u);
+        ml = __builtin_amdgcn_alignbit(ml, (uint32_t)(l[i] - vp), 31u);
+      }
+      ne += __builtin_popcount(me);
+      nl += __builtin_popcount(ml);
+    }
+    return ne - nl;
+  }
+  int delta = 0;
+#pragma unroll 1
+  for (int j = 0; j < ncols; ++j) delta += (int)(enter(vt[j]) < vp) - (int)(leave(vt[j]) < vp);
+  return delta;
+}
+
 // Rank selection for one window (wave-uniform arguments): given a pivot
 // ordinal p and the number c of window members with ordinal < p, return the
 // member ordinal m with exactly k members below it.  The omnigram is tested
@@ -267,66 +351,44 @@ __device__ __forceinline__ int lane_select(int& p, int& c, int k, uint32_t cxy, 
                                            const Fp& f, const uint16_t* om,
                                            const short2* rsp, int& groups) {
   const bool up = c <= k;
-  int need = up ? k - c : c - 1 - k;
-  int q = up ? (p & ~7) : ((p - 1) & ~7);
-  const int need0 = need;   // members passed = need0 - need
-  int m = -1, it = 0;
-  uint32_t bits = 0;
-  // first (partial) group: only ordinals in [p, T) (up) or [0, p) (down);
-  // p > 0 whenever the walk goes down, so q >= 0
-  {
-    const uint4 g = *reinterpret_cast<const uint4*>(om + max(q, 0));
-    uint32_t range;
-    if (up) {
-      const int hi = T - q;   // entries j < hi are below T
-      range = (0xffu << (p - q)) & (hi >= 8 ? 0xffu : ((1u << max(hi, 0)) - 1u));
-    } else {
-      range = (1u << (p - q)) - 1u;
-    }
-    bits = group_mask<SHAPE>(g, cxy, f, rsp) & range;
-    const int cnt = __builtin_popcount(bits);
+  const int need0 = up ? k - c : c - 1 - k;   // members to pass before the one sought
+  const int step = up ? 8 : -8;
+  int q = (up ? p : p - 1) & ~7;   // p > 0 whenever the walk goes down, so q >= 0
+  // first (partial) group: only ordinals in [p, ..) (up) or [0, p) (down)
+  uint32_t bits = group_mask<SHAPE>(*reinterpret_cast<const uint4*>(om + max(q, 0)), cxy, f, rsp) &
+                  ((0xffu << (p - q)) ^ (up ? 0u : 0xffu));
+  int over = __builtin_popcount(bits) - need0;   // > 0: the member sought is in this group
+  const int q0 = q;
+  q += step;
+  // full groups, counted only.  One exit test and nothing kept by choice: an
+  // exit leaves q one step ahead, and the members still to pass are recovered
+  // from the last group's count.
+  int it = 1;
+  while (over <= 0 && (unsigned)q < (unsigned)T && it < budget) {
+    bits = group_mask<SHAPE>(*reinterpret_cast<const uint4*>(om + q), cxy, f, rsp);
+    over += __builtin_popcount(bits);
+    q += step;
     ++it;
-    if (need < cnt) {
-      m = q;   // selection below
-    } else {
-      need -= cnt;
-      q += up ? 8 : -8;
-    }
   }
-  // full groups: count members only
-  while (m < 0 && (up ? q < T : q >= 0) && it < budget) {
-    const uint4 g = *reinterpret_cast<const uint4*>(om + q);
-    bits = group_mask<SHAPE>(g, cxy, f, rsp);
-    const int cnt = __builtin_popcount(bits);
-    ++it;
-    if (need < cnt) {
-      m = q;
-      break;
-    }
-    need -= cnt;
-    q += up ? 8 : -8;
-  }
-  if (m >= 0) {
-    // the need-th member of the group from the bottom going up, from the
-    // top going down (= member cnt - 1 - need from the bottom): the n-th set
-    // bit of the 8-bit mask by halving (nibble, pair, bit)
+  int m = -1;
+  if (over > 0) {
+    // the member sought, counted from the group's far end: over - 1 members
+    // lie beyond it (above it going up, below it going down)
+    const int n = up ? __builtin_popcount(bits) - over : over - 1;
     uint32_t x = bits;
-    int n = up ? need : __builtin_popcount(bits) - 1 - need;
-    int jsel = 0;
+    int i = n, jsel = 0;   // n-th set bit by halving (nibble, pair, bit)
     int cn = __builtin_popcount(x & 15u);
-    if (n >= cn) { n -= cn; jsel += 4; x >>= 4; }
+    if (i >= cn) { i -= cn; jsel += 4; x >>= 4; }
     cn = __builtin_popcount(x & 3u);
-    if (n >= cn) { n -= cn; jsel += 2; x >>= 2; }
-    if (n >= (int)(x & 1u)) jsel += 1;
-    m = q + jsel;
+    if (i >= cn) { i -= cn; jsel += 2; x >>= 2; }
+    if (i >= (int)(x & 1u)) jsel += 1;
+    m = q - step + jsel;
+  } else {
+    // frontier: the first ordinal not passed, and the members below it
+    p = min(max(up ? q : q + 8, 0), T);
+    c += up ? over + need0 : -over - need0;
   }
-  groups += it;
-  if (m < 0) {
-    p = up ? q : q + 8;
-    if (p < 0) p = 0;
-    if (p > T) p = T;
-    c += up ? need0 - need : need - need0;   // members below the frontier
-  }
+  groups += (up ? q - q0 : q0 - q) >> 3;
   return m;
 }
 
@@ -468,44 +530,46 @@ __device__ __forceinline__ int row_select(bool act, int p, int c, int k, uint32_
   const int j = threadIdx.x & 15;
   const bool up = c <= k;
   int need = up ? k - c : c - 1 - k;   // members to pass before the one sought
-  int q = up ? (p & ~7) : ((p - 1) & ~7);
+  const int q0 = (up ? p : p - 1) & ~7;
+  int q = up ? q0 + 8 * j : q0 - 8 * j;   // this lane's group
+  const int step = up ? 128 : -128;
+  // the first step's first group is partial
+  uint32_t range = j == 0 ? (0xffu << (p - q0)) ^ (up ? 0u : 0xffu) : ~0u;
   bool done = !act;
   int res = -1;
   const int cap = (T >> 7) + 2;
   for (int it = 0; it < cap; ++it) {
     if (wave_ballot(!done) == 0) break;
-    const int qj = up ? q + 8 * j : q - 8 * j;
-    const bool valid = !done && (up ? qj < T : qj >= 0);
-    uint32_t bits = 0;
-    if (valid) {
-      const uint4 g = *reinterpret_cast<const uint4*>(om + qj);
-      bits = group_mask<SHAPE>(g, cxy, f, rsp);
-      if (it == 0 && j == 0) bits &= up ? (0xffu << (p - q)) : ((1u << (p - q)) - 1u);
-      ++groups;
-    }
+    // (groups out of range read ordinal 0's and count nothing)
+    const bool valid = !done && (unsigned)q < (unsigned)T;
+    const uint4 g = *reinterpret_cast<const uint4*>(om + (valid ? q : 0));
+    const uint32_t bits = valid ? group_mask<SHAPE>(g, cxy, f, rsp) & range : 0u;
+    range = ~0u;
+    groups += valid;
     const int pc = __builtin_popcount(bits);
     const int incl = row_incl_scan16(pc);
-    const int tot = __shfl(incl, (int)(threadIdx.x | 15u), 64);
-    const int before = incl - pc;
-    int cand = -1;
-    if (valid && before <= need && need < incl) {
-      const int n = need - before;
-      cand = up ? qj + nth_bit8(bits, n) : qj + nth_bit8(bits, pc - 1 - n);
-    }
+    const int tot = row_sum16(pc);
+    const bool hit = !done && need < tot;   // (row-uniform)
     // (the row's candidate reaches its lanes only on an iteration where some
     // row finds its member)
-    if (wave_ballot(!done && need < tot) != 0) cand = row_max16(cand);
-    if (!done) {
-      if (need < tot) {
+    if (wave_ballot(hit) != 0) {
+      const int n = need - (incl - pc);
+      int cand = -1;
+      if (hit && n >= 0 && n < pc) cand = q + nth_bit8(bits, up ? n : pc - 1 - n);
+      cand = row_max16(cand);
+      if (hit) {
         res = cand;
         done = true;
-      } else {
-        need -= tot;
-        q += up ? 128 : -128;
-        if (up ? q >= T : q < 0) {
-          done = true;
-          c_end = up ? k - need : k + 1 + need;
-        }
+      }
+    }
+    if (!done) {
+      need -= tot;
+      q += step;
+      // the row's first group of the next step
+      const int qn = up ? q - 8 * j : q + 8 * j;
+      if ((unsigned)qn >= (unsigned)T) {
+        done = true;
+        c_end = up ? k - need : k + 1 + need;
       }
     }
   }
@@ -839,10 +903,10 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   const int nr4 = (a.nrows + 3) & ~3;
   short2* rsp = reinterpret_cast<short2*>(smem + a.off_tab + 128);   // after wsum (32 words)
   int2* hrow = reinterpret_cast<int2*>(smem + a.off_tab + 128 + 4 * nr4);
-  int4* vtab = reinterpret_cast<int4*>(smem + a.off_tab + 128 + 12 * nr4);
+  uint32_t* vtab = reinterpret_cast<uint32_t*>(smem + a.off_tab + 128 + 12 * nr4);
 
   const int t = threadIdx.x;
-  const int lane = t & 63, wid = t >> 6;
+  const int lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);   // (wave-uniform)
   const int tx0 = (tile % a.tiles_x) * a.tw, ty0 = (tile / a.tiles_x) * a.th;
   const long long clk0 = a.counters ? (long long)clock64() : 0;
   long long clk_load = clk0;
@@ -856,11 +920,15 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   int Tv = T;        // ordinals [0, Tv) are valid omnigram entries
   int mlo = 0;       // smallest ordinal a member may have
 
-  // footprint tables: row spans, per-row horizontal offsets, per-column
-  // vertical offsets (down: entering, leaving; up: entering, leaving), all
-  // relative to the window centre.  Planes with windows of their own
-  // (multi_fp) rebuild them per plane inside the box of the plan, whose
-  // offsets (a.dx_min, a.dy_min) still place the centres.
+  // footprint tables: row spans, per-row horizontal offsets relative to the
+  // window centre, per-column vertical offsets (entering | leaving << 16)
+  // relative to the box position one row above and at the left end of the
+  // window's offset rectangle: one table for slides down, one for slides up,
+  // each padded to a multiple of eight columns whose two offsets cancel
+  // (windows of fewer than four columns: not padded).  Planes with windows of
+  // their own (multi_fp) rebuild them per plane inside the box of the plan,
+  // whose offsets (a.dx_min, a.dy_min) still place the centres.
+  auto vcols8 = [](int ncols) { return ncols >= 4 ? (ncols + 7) & ~7 : 0; };
   auto build_tables = [&](const short2* spans, int nrows, int ncols, int dx_min, int dy_min) {
     for (int i = t; i < nrows; i += kThreads) {
       const short2 s = spans[i];
@@ -868,20 +936,25 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
       const int dy = dy_min + i;
       hrow[i] = make_int2(dy * a.pitch + s.y + 1, dy * a.pitch + s.x);
     }
-    for (int j = t; j < ncols; j += kThreads) {
-      const short2 s = spans[nrows + j];
-      const int dx = dx_min + j;
-      vtab[j] = make_int4((s.y + 1) * a.pitch + dx, s.x * a.pitch + dx,
-                          (s.x - 1) * a.pitch + dx, s.y * a.pitch + dx);
+    const int n8 = vcols8(ncols), n = n8 ? n8 : ncols;
+    for (int j = t; j < n; j += kThreads) {
+      const short2 s = j < ncols ? spans[nrows + j] : make_short2(0, 0);
+      // rows from one above the rectangle's top
+      const uint32_t r0 = (uint32_t)((s.x - dy_min + 1) * a.pitch + j);
+      const uint32_t r1 = (uint32_t)((s.y - dy_min + 1) * a.pitch + j);
+      const uint32_t P = (uint32_t)a.pitch;
+      vtab[j] = j < ncols ? (r1 + P) | (r0 << 16) : 0u;
+      vtab[n + j] = j < ncols ? (r0 - P) | (r1 << 16) : 0u;
     }
   };
   const bool mfp = GEN && a.multi_fp;
   Fp f{a.limit, a.dy_min, a.nrows};
-  int fcols = a.ncols;
+  int fcols = a.ncols, fdx_min = a.dx_min;
   if (mfp) {
     const auto& p0 = a.pfp[0];
     f = Fp{p0.limit, p0.dy_min, p0.nrows};
     fcols = p0.ncols;
+    fdx_min = p0.dx_min;
     build_tables(p0.spans, p0.nrows, p0.ncols, p0.dx_min, p0.dy_min);
   } else {
     build_tables(a.spans, a.nrows, a.ncols, a.dx_min, a.dy_min);
@@ -1256,18 +1329,30 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   long long seed_clk = 0, row_clk = 0, sweep_clk = 0;
   const int tw = a.tw, segs = a.segs, R = a.band_rows;
   const int seg = lane / tw, col = lane - seg * tw;
-  const int band = wid * segs + seg;
-  const int row0 = band * R;                 // first output row of this lane's band
+  // Two waves (one, chained) work on the same bands: `half` 0 sweeps up from
+  // the band's first solved row, half 1 down.
+  constexpr bool PAIR = !CHAIN;
+  constexpr int NH = PAIR ? 2 : 1, CW = PAIR ? 8 : 16;   // waves per band, chunk width
+  const int half = PAIR ? wid & 1 : 0, wband = PAIR ? wid >> 1 : wid;
+  const bool up = PAIR && half == 0;
+  const int RB = NH * R;                     // rows of a band
+  const int rows_lim = min(a.h - ty0, a.th);   // tile rows inside the image
+  // the row of band b that its waves start from (the middle one, or the last
+  // inside the image; outside the band or the image if it has no rows)
+  auto start_row = [&](int b) { return PAIR ? min(b * RB + R, rows_lim - 1) : b * RB; };
+  const int band0 = (wband * segs + seg) * RB;       // first output row of this lane's band
+  const int row0 = start_row(wband * segs + seg);    // the row it starts from
   const int cxl = col - a.dx_min;            // lane's window centre, box coords
   const int cols_in = min(tw, a.w - tx0);
   const int nq = GEN ? a.nq : 1;
   for (int q = 0; q < nq; ++q) {
+  if (GEN && q > 0) __syncthreads();   // the previous plane's tables and exchange are done with
   if (mfp && q > 0) {
-    // this plane's window: every wave is done with the previous tables
+    // this plane's window
     const auto& pq = a.pfp[q];
-    __syncthreads();
     f = Fp{pq.limit, pq.dy_min, pq.nrows};
     fcols = pq.ncols;
+    fdx_min = pq.dx_min;
     build_tables(pq.spans, pq.nrows, pq.ncols, pq.dx_min, pq.dy_min);
     __syncthreads();
   }
@@ -1296,16 +1381,18 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   // sweep's lanes (lane = seg * tw + col) by a lane shuffle per round.
   {
     const int g = lane >> 4, j = lane & 15;
-    const int nchb = (cols_in + 15) >> 4;       // chunks per band row
+    const int nchb = (cols_in + CW - 1) / CW;   // chunks per band row
     const int nch = segs * nchb;
     int lp = 0, lc = 0;   // pivot and count of the last seed solved
-    for (int r0 = 0; r0 < nch; r0 += 4) {
+    bool got = false;     // this lane's column is solved by this wave
+    for (int r0 = 4 * half; r0 < nch; r0 += 4 * NH) {
       // this row's chunk: band s, first column c0, len columns
       const int ch = r0 + g;
-      const int sb = ch / nchb, c0 = (ch - sb * nchb) << 4;
-      const int brow = (wid * segs + sb) * R;
-      const bool ok = ch < nch && brow < a.th && ty0 + brow < a.h && !(fw && wid == 0 && sb == 0);
-      const int len = ok ? min(16, cols_in - c0) : 0;
+      const int sb = ch / nchb, c0 = (ch - sb * nchb) * CW;
+      const int brow = start_row(wband * segs + sb);
+      const bool ok = ch < nch && brow >= (wband * segs + sb) * RB && brow < rows_lim &&
+                      !(fw && wid == 0 && sb == 0);
+      const int len = ok ? min(CW, cols_in - c0) : 0;
       const int cy = brow - a.dy_min;
       // ranks of the chunk's pixels, lane j holding column c0 + j
       const int krow = rank_at<GEN>(a, q, k0, tx0 + c0 + j, ty0 + brow, ok && j < len);
@@ -1319,32 +1406,33 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
       for (int gg = 0; gg < 4; ++gg) {
         const int chg = r0 + gg;
         if (chg >= nch) break;
-        const int sg = chg / nchb, c0g = (chg - sg * nchb) << 4;
-        const int browg = (wid * segs + sg) * R;
-        if (browg >= a.th || ty0 + browg >= a.h || (fw && wid == 0 && sg == 0)) continue;
+        const int sg = chg / nchb, c0g = (chg - sg * nchb) * CW;
+        const int browg = start_row(wband * segs + sg);
+        if (browg < (wband * segs + sg) * RB || browg >= rows_lim || (fw && wid == 0 && sg == 0))
+          continue;
         const int kseed = GEN ? __builtin_amdgcn_readlane(krow, 16 * gg) : k0;
         const int cyg = browg - a.dy_min;
         const long long cs0 = a.counters ? (long long)clock64() : 0;
         int ms, sp, sc;
-        if (c0g == 0) {
+        if (c0g == 0 || (PAIR && gg == 0)) {
           int ep = 0, ec = 0;
-          ms = seed_solve<KT, SHAPE, BR, !GS>(0 - a.dx_min, cyg, Tv, hshift, kseed, a, f, om, I,
+          ms = seed_solve<KT, SHAPE, BR, !GS>(c0g - a.dx_min, cyg, Tv, hshift, kseed, a, f, om, I,
                                               hist, rsp, blocks, ep, ec);
           ++seeds;
           sp = (BR && ms < 0) ? ep : ms;
           sc = (BR && ms < 0) ? ec : kseed;
         } else {
-          const int cx0 = c0g - 16 - a.dx_min;   // previous seed's centre
+          const int cx0 = c0g - CW - a.dx_min;   // previous seed's centre
           const int jb = cyg * a.pitch + cx0;
           int d = 0;
-          for (int e = lane; e < (f.nrows << 4); e += 64) {
-            const int2 o = hrow[e >> 4];
-            const int tt = e & 15;
-            d += (int)(I[jb + o.x + tt] < (uint32_t)lp) - (int)(I[jb + o.y + tt] < (uint32_t)lp);
-          }
+          const int jt = jb + lane % CW;   // 64 / CW rows per step, four steps in flight
+          constexpr int RS = 64 / CW;
+          int i = lane / CW;
+          for (; i < f.nrows; i += 4 * RS) d += rows_below<4, RS>(hrow, I, f.nrows, i, jt, lp);
           const int cnt = lc + wave_sum(d);
           int c_end = 0;
-          ms = wave_select<SHAPE>(lp, cnt, kseed, pack_centre<SHAPE>(cx0 + 16, cyg), Tv, f, om, rsp, groups, c_end);
+          ms = wave_select<SHAPE>(lp, cnt, kseed, pack_centre<SHAPE>(cx0 + CW, cyg),
+                                  Tv, f, om, rsp, groups, c_end);
           sp = (!BR || ms >= 0) ? ms : (cnt <= kseed ? Tv : 1);
           sc = (!BR || ms >= 0) ? kseed : c_end;
         }
@@ -1375,11 +1463,10 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
         const int base = cy * a.pitch + cxp;
         int d = 0;
         if (act) {
-          // rows beyond the footprint read the centre twice and cancel
-          for (int i = j; i < f.nrows; i += 16) {
-            const int2 o = hrow[i];
-            d += (int)(I[base + o.x] < (uint32_t)hp) - (int)(I[base + o.y] < (uint32_t)hp);
-          }
+          // four of the lane's rows in flight, single ones at the end
+          int i = j;
+          for (; i + 48 < f.nrows; i += 64) d += rows_below<4, 16>(hrow, I, f.nrows, i, base, hp);
+          for (; i < f.nrows; i += 16) d += rows_below<1, 16>(hrow, I, f.nrows, i, base, hp);
         }
         const int cnt = hc + row_sum16(d);
         int c_end = 0;
@@ -1403,9 +1490,9 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
         }
       }
       // hand this round's columns to the sweep lanes
-      const int chu = seg * nchb + (col >> 4);
+      const int chu = seg * nchb + col / CW;
       const bool mine = lane < segs * tw && col < cols_in && chu >= r0 && chu < r0 + 4;
-      const int src = mine ? (((chu - r0) << 4) | (col & 15)) : 0;
+      const int src = mine ? (((chu - r0) << 4) | (col % CW)) : 0;
       const int mv = __shfl(m_l, src, 64), pv = __shfl(vp_l, src, 64);
       const int cv = __shfl(vc_l, src, 64), xv = __shfl(miss_l, src, 64);
       if (mine) {
@@ -1413,6 +1500,22 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
         vp = pv;
         vc = cv;
         miss = xv;
+        got = true;
+      }
+    }
+    if constexpr (PAIR) {
+      // the columns the other wave of the pair solved, through the two
+      // waves' histograms (their seeds are done)
+      int4* own = reinterpret_cast<int4*>(hist);
+      const int4* other = reinterpret_cast<const int4*>(hist_all + (wid ^ 1) * kHistWords);
+      if (got) own[lane] = make_int4(m, vp, vc, miss);
+      __syncthreads();
+      if (!got) {
+        const int4 v = other[lane];
+        m = v.x;
+        vp = v.y;
+        vc = v.z;
+        miss = v.w;
       }
     }
   }
@@ -1428,38 +1531,38 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   }
   {
     const int gx = tx0 + col, gy = ty0 + row0;
-    const bool own = lane < segs * tw && col < cols_in && row0 < a.th && gy < a.h &&
-                     !(fw && wid == 0 && seg == 0);
+    const bool own = lane < segs * tw && col < cols_in && row0 >= band0 && row0 < rows_lim &&
+                     !up && !(fw && wid == 0 && seg == 0);
     if (own && !miss) store_out<KT, GATHER>(a, outq, gx, gy, kbuf, crev, om, m, blo, gx0, gy0);
     if (BR) push_misses(a, own && miss, gx, gy);
     if (CHAIN && own && row0 == a.th - 1) fwd[col] = om[m];
   }
 
-  // 4b. vertical sweep down each band (lanes whose column or row is
-  // outside the image sit out)
+  // 4b. vertical sweeps up and down each band from its first solved row
+  // (lanes whose column or row is outside the image sit out)
   const bool in_cols = lane < segs * tw && col < cols_in;
-  const int rows_lim = min(a.h - ty0, a.th);   // tile rows inside the image
-  const int rows_in = rows_lim - row0;          // rows of this lane's band inside both
-  const int r_end = min(R, __builtin_amdgcn_readfirstlane(max(0, rows_lim - wid * segs * R)));
+  // rows this lane has to go: up to the band's first row, or down to its last
+  const int rows_in = in_cols ? (up ? row0 - band0 : min(band0 + RB, rows_lim) - 1 - row0) : 0;
+  const int r_end = PAIR ? R : R - 1;
   // (the forwarded band starts one row higher, at the row above the tile)
   const int r_begin = fw && wid == 0 ? 0 : 1;
-  for (int r = r_begin; r < r_end; ++r) {
-    const bool lane_active = in_cols && r < rows_in && (r > 0 || fw_lanes);
-    const int gx = tx0 + col, gy = ty0 + row0 + r;
+  const int dir = up ? -1 : 1;
+  const int n8 = vcols8(fcols);
+  const uint32_t* vt = vtab + (up ? (n8 ? n8 : fcols) : 0);
+  for (int r = r_begin; r <= r_end; ++r) {
+    const bool lane_active = r <= rows_in && (r > 0 || fw_lanes);
+    if (PAIR && wave_ballot(lane_active) == 0) break;
+    const int row = row0 + dir * r;
+    const int gx = tx0 + col, gy = ty0 + row;
     const int kl = rank_at<GEN>(a, q, k0, gx, gy, lane_active);
-    const int cy_prev = row0 + r - 1 - a.dy_min;
-    const int lbase = cy_prev * a.pitch + cxl;
-    int delta = 0;
-    if (lane_active) {
-#pragma unroll 4
-      for (int j = 0; j < fcols; ++j) {
-        const int4 o = vtab[j];
-        delta += (int)(I[lbase + o.x] < vp) - (int)(I[lbase + o.y] < vp);
-      }
-    }
+    const int cy_prev = row - dir - a.dy_min;
+    // LDS address of the previous window's rectangle, one row above it
+    const uint32_t lb = lds_address(I) +
+                        (uint32_t)(2 * ((cy_prev + f.dy_min - 1) * a.pitch + cxl + fdx_min));
+    const int delta = lane_active ? slide_count(vt, n8, fcols, lb, vp) : 0;
     int pl = vp, cl = vc + delta;
     int mnew = m, esc = 0;
-    const uint32_t cxy = pack_centre<SHAPE>(cxl, row0 + r - a.dy_min);
+    const uint32_t cxy = pack_centre<SHAPE>(cxl, row - a.dy_min);
     if (lane_active) {
       mnew = lane_select<SHAPE>(pl, cl, kl, cxy, kLaneBudget, Tv, f, om, rsp, groups);
       if (BR && mnew < 0 && (pl <= 0 || pl >= Tv)) {
@@ -1513,7 +1616,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
     if (lane_active && !esc)
       store_out<KT, GATHER>(a, outq, gx, gy, kbuf, crev, om, m, blo, gx0, gy0);
     if (BR) push_misses(a, lane_active && esc, gx, gy);
-    if (CHAIN && lane_active && row0 + r == a.th - 1) fwd[col] = om[m];
+    if (CHAIN && lane_active && row == a.th - 1) fwd[col] = om[m];
   }
   if (a.counters) {
     const long long clk3 = (long long)clock64();
