@@ -53,23 +53,21 @@ double bits_us(const Variant& v, int W, int H, int es, int lds_max, long long w,
 }
 
 // The tile engine on the same image, near the line where the two paths meet:
-// per pixel as at 4096 x 4096 (disc 8 to 16: uint8 1.21 to 1.26 ms, uint16
-// 1.00 to 1.06, float32 1.35 to 1.50), and no less than the few tiles of a
-// small image take (256 x 256 to 641 x 479, disc 4 to 20: 75 to 180 us).  At
-// 4096 x 4096 the bit planes win up to disc 12 for uint16 (0.90 against 1.00
-// ms; disc 13 1.02 against 1.00), disc 17 for uint8 (disc 16 0.87 against
-// 1.26) and disc 10 for float32 (0.98 against 1.40; disc 12 1.8 against
-// 1.35), and by 2.9x / 6.3x / 2.1x at disc 8.
+// what it takes at least, by the pixel (4096 x 4096, disc 8 to 16: uint8 1.21
+// ms, uint16 1.00, float32 1.35 before its first rows were halved, about 0.87
+// times that since) and for one round of the smallest tiles.  At 4096 x 4096
+// the bit planes win up to disc 11 for uint16 (0.64 ms), disc 16 for uint8
+// (0.87) and disc 10 for float32 (0.98).
 double tile_us(int dtype, long long w, long long h) {
-  const double ns = dtype == MF_U8 ? 0.073 : dtype == MF_U16 ? 0.060 : 0.083;
-  return std::max(90.0, 1e-3 * ns * (double)w * (double)h);
+  const double ns = dtype == MF_U8 ? 0.063 : dtype == MF_U16 ? 0.052 : 0.072;
+  return std::max(25.0, 1e-3 * ns * (double)w * (double)h);
 }
 
 }  // namespace
 
 int bits_threads(int v) { return kVariants[v].threads; }
 
-int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, ImageDesc* d) {
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d) {
   int tw = 0, th = 0;
   get_override(&tw, &th);
   // a tile shape asks for the tile engine, and the work counters count its work
@@ -82,7 +80,7 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, Imag
     pairs += (fp->row_hi[i] - fp->row_lo[i] + 2) / 2;
   }
   int best = -1;
-  double best_us = tile_us(dtype, w, h);
+  double best_us = 1e30;
   for (int i = 0; i < kBitsVariants; ++i) {
     const Variant& v = kVariants[i];
     if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
@@ -93,6 +91,20 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, Imag
     }
   }
   if (best < 0) return MF_ERR_UNSUPPORTED;
+  const double floor_us = tile_us(dtype, w, h);
+  // Not clearly faster: against the tile plan, whose estimate is for smooth
+  // content.  Noise takes up to a quarter less, so over more than two rounds
+  // of tiles the line lies a tenth lower (uint8 2048 x 2048 disc 20: 327 us
+  // here, tiles 345 on smooth content and 258 on noise; disc 14: 162 here,
+  // the tiles more than 264).
+  if (best_us > floor_us) {
+    ImageDesc t{};
+    if (choose_plan(dtype, fp, lds_max, 33, &t, w, h, cus) == MF_OK) {
+      const long long tiles = (long long)((w + t.tw - 1) / t.tw) * ((h + t.th - 1) / t.th);
+      const double us = (tiles > 2LL * cus ? 0.9 : 1.0) * plan_us(t, w, h, cus);
+      if (best_us > std::max(floor_us, us)) return MF_ERR_UNSUPPORTED;
+    }
+  }
   const Variant& v = kVariants[best];
   *d = ImageDesc{};
   d->bits = 1 + best;

@@ -486,7 +486,7 @@ int learned_plan(int dtype, const mf_footprint* fp, int w, int h, LearnedPlan* l
   mf::ImageDesc own{};
   const bool have_own =
       w > 0 && h > 0 &&
-      mf::choose_plan(dtype, fp, lp->di.lds_max, 33, &own, w, h, lp->di.cus) == MF_OK;
+      mf::choose_plan(dtype, fp, lp->di.lds_max, 33, &own, w, h, lp->di.cus, false) == MF_OK;
   mf::ImageDesc base{};
   if ((rc = mf::choose_plan_tall(dtype, fp, lp->di.lds_max, 33, &base))) return rc;
   if ((rc = mf::make_plan_br(dtype, fp, lp->di.lds_max, base.tw, base.th, &lp->br)))

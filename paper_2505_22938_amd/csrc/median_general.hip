@@ -273,7 +273,7 @@ int median_filter_windows(const void* img, int w, int h, size_t stride_bytes, in
   double gain[MF_MAX_RANK_OUTPUTS];
   for (int q = 0; q < nouts; ++q) {
     ImageDesc p{};
-    if ((rc = choose_plan(dtype, outs[q].footprint, di.lds_max, 33, &p, w, h, di.cus))) return rc;
+    if ((rc = choose_plan(dtype, outs[q].footprint, di.lds_max, 33, &p, w, h, di.cus, false))) return rc;
     boxT[q] = p.T;
     gain[q] = (double)p.T / ((double)p.tw * p.th) * (double)outs[q].footprint->taps;
     order[q] = q;

@@ -162,7 +162,7 @@ int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
   rc = footprint_device_table(fp, dev, &table, stream);
   if (rc) return rc;
   ImageDesc a{};
-  if (bits_plan(dtype, fp, di.lds_max, w, h, &a) != MF_OK &&
+  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, &a) != MF_OK &&
       (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
     return rc;
   bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, rank, table);
@@ -185,7 +185,7 @@ int launch_chained(const void* img, int w, int h, size_t stride_bytes, int dtype
   const void* table = nullptr;
   if ((rc = footprint_device_table(fx, dev, &table, stream))) return rc;
   ImageDesc a{};
-  if ((rc = choose_plan(dtype, fx, di.lds_max - 128, 33, &a, w, h, di.cus))) return rc;
+  if ((rc = choose_plan(dtype, fx, di.lds_max - 128, 33, &a, w, h, di.cus, false))) return rc;
   if (a.gs) return MF_ERR_UNSUPPORTED;   // chained tiles re-rank in LDS
   a.off_fwd = a.lds_bytes;
   a.lds_bytes += 128;

@@ -152,10 +152,12 @@ int device_info(int dev, DeviceInfo* out);
 int make_plan(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, ImageDesc* d);
 int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, ImageDesc* d);
 // w, h, cus (image size and compute units, 0 = unknown) let the default
-// choice keep enough tiles per CU.  choose_plan_tall: the override or the
+// choice keep enough tiles per CU and, with `spread`, take the shape that
+// suits a small image (plan_us: its estimated time).  choose_plan_tall: the override or the
 // tallest default shape, ignoring the tuned table (bracketed tiles).
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
-                int w = 0, int h = 0, int cus = 0);
+                int w = 0, int h = 0, int cus = 0, bool spread = true);
+double plan_us(const ImageDesc& c, int w, int h, int cus);
 int choose_plan_tall(int dtype, const mf_footprint* fp, int lds_max, int imax_cap,
                      ImageDesc* d);
 // Bracketed-tile plan (8/16-bit keys) for a given shape: region A holds only
@@ -205,7 +207,7 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
 PlainKernelFn pick_general_kernel(const ImageDesc& d);
 // Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
 // kernel, and launch with a complete plan.
-int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, ImageDesc* d);
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d);
 PlainKernelFn pick_bits_u8(int v);
 PlainKernelFn pick_bits_u16(int v);
 PlainKernelFn pick_bits_f32(int v);

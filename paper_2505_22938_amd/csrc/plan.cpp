@@ -336,16 +336,69 @@ static int default_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
   return MF_OK;
 }
 
+// Estimated time in microseconds of a tile plan on a w x h image whose tiles
+// run one per CU in rounds: a fixed part, the box (load and sort) and, for
+// the tile's pixels, walks in proportion to the box.  Measured on smooth
+// uint16 content (estimate), us a round: 641 x 479 disc 24, 64x64 / 64x32 /
+// 32x48 / 32x32 / 16x16 tiles 116 / 75 / 59 / 46 / 28 (96 / 58 / 50 / 41 /
+// 32); disc 64, 64x64 (global scratch) / 64x32 / 32x48 / 16x16 227 / 151 /
+// 127 / 77 (254 / 146 / 122 / 72); 1500 x 1200 disc 32, 64x64 / 64x128 109 /
+// 254 (119 / 257).  float32 log-normal 641 x 479: disc 24, 64x64 / 16x16
+// 103 / 41 (98 / 44), disc 64, 64x64 / 32x32 (global scratch) / 16x16 270 /
+// 191 / 106 (326 / 197 / 103).
+double plan_us(const ImageDesc& c, int w, int h, int cus) {
+  const bool f32 = c.kt == MF_F32;
+  const double fixed = f32 ? 30.0 : 22.0;
+  const double key = f32 ? (c.gs ? 6.0 : 3.4) : (c.gs ? 2.6 : 2.2);
+  const double walk = (f32 ? 0.5 : 0.9) * 64.0 / (c.tw * c.segs);
+  const double T = c.T * 1e-3, px = c.tw * c.th * 1e-3;
+  const long long tiles = (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
+  return (fixed + key * T + walk * T * px) * (double)((tiles + cus - 1) / cus);
+}
+
+// Images of fewer than about four tiles per CU: the shape whose rounds of
+// tiles take least.  A call then lasts a whole number of tiles whatever part
+// of the last round is filled, so the best shape is often the largest that
+// still fits one round (2-byte smooth 641 x 479: 88 tiles of 64x64 against
+// 210 of 32x48, disc 24 115 -> 59 us, disc 64 225 -> 127; 1500 x 1200 disc
+// 64: 264 tiles of 64x112 in two rounds 602 us, 240 of 64x128 in one 445).
+// The default is kept unless the estimate gains 8 %, and against shapes of
+// more than two rounds, where CUs drift apart and rounds stop counting whole
+// (1500 x 1200 disc 96: 608 tiles of 48x64 913 us, 513 of 56x64 751).
+static void spread_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h,
+                        int cus, ImageDesc* d) {
+  const long long tiles = (long long)((w + d->tw - 1) / d->tw) * ((h + d->th - 1) / d->th);
+  if (tiles * 20 >= 4LL * cus * 19) return;
+  static const int tws[] = {64, 48, 32, 16};
+  static const int ths[] = {128, 112, 96, 80, 64, 48, 32, 16};
+  double best = 0.92 * plan_us(*d, w, h, cus);
+  for (int tw : tws)
+    for (int th : ths) {
+      ImageDesc c{};
+      if (plan_shape(dtype, fp, lds_max, imax_cap, tw, th, &c) != MF_OK) continue;
+      const long long n = (long long)((w + tw - 1) / tw) * ((h + th - 1) / th);
+      if (n > 2LL * cus) continue;
+      const double us = plan_us(c, w, h, cus);
+      if (us < best) {
+        best = us;
+        *d = c;
+      }
+    }
+}
+
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
-                int w, int h, int cus) {
+                int w, int h, int cus, bool spread) {
   int tw = 0, th = 0;
   get_override(&tw, &th);
   if (tw > 0) return plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d);
   if (tuned_shape(dtype, fp, &tw, &th) &&
       plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d) == MF_OK)
     return MF_OK;
-  const long long fill = w > 0 && h > 0 && cus > 0 ? 4LL * cus : 0;
-  return default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), w, h, fill, d);
+  const bool sized = w > 0 && h > 0 && cus > 0;
+  const int rc = default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), w, h,
+                              sized ? 4LL * cus : 0, d);
+  if (rc == MF_OK && sized && spread) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+  return rc;
 }
 
 int choose_plan_tall(int dtype, const mf_footprint* fp, int lds_max, int imax_cap,
