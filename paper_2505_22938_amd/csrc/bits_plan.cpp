@@ -67,7 +67,8 @@ double tile_us(int dtype, long long w, long long h) {
 
 int bits_threads(int v) { return kVariants[v].threads; }
 
-int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d) {
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d,
+              double* us) {
   int tw = 0, th = 0;
   get_override(&tw, &th);
   // a tile shape asks for the tile engine, and the work counters count its work
@@ -84,10 +85,10 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   for (int i = 0; i < kBitsVariants; ++i) {
     const Variant& v = kVariants[i];
     if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
-    const double us = bits_us(v, W, H, es, lds_max, w, h);
-    if (us < best_us) {
+    const double t = bits_us(v, W, H, es, lds_max, w, h);
+    if (t < best_us) {
       best = i;
-      best_us = us;
+      best_us = t;
     }
   }
   if (best < 0) return MF_ERR_UNSUPPORTED;
@@ -101,10 +102,11 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
     ImageDesc t{};
     if (choose_plan(dtype, fp, lds_max, 33, &t, w, h, cus) == MF_OK) {
       const long long tiles = (long long)((w + t.tw - 1) / t.tw) * ((h + t.th - 1) / t.th);
-      const double us = (tiles > 2LL * cus ? 0.9 : 1.0) * plan_us(t, w, h, cus);
-      if (best_us > std::max(floor_us, us)) return MF_ERR_UNSUPPORTED;
+      const double tus = (tiles > 2LL * cus ? 0.9 : 1.0) * plan_us(t, w, h, cus);
+      if (best_us > std::max(floor_us, tus)) return MF_ERR_UNSUPPORTED;
     }
   }
+  if (us) *us = best_us;
   const Variant& v = kVariants[best];
   *d = ImageDesc{};
   d->bits = 1 + best;

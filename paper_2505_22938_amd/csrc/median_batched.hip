@@ -5,8 +5,9 @@
 // mf_plan_create builds, per image, the plain filter's plan (tuned shape if
 // one is recorded) and a device descriptor table, then splits all tiles of
 // all images into groups that share a kernel instance (key type, footprint
-// form, register capacity or global scratch), so that each instance keeps
-// the register allocation of the plain kernel for that variant.  A group is
+// form, register capacity or global scratch, or bit-plane variant), so that
+// each instance keeps the register allocation of the plain kernel for that
+// variant.  A group is
 // a slice of one tile queue, ordered longest-estimated-first, run by one
 // launch: one workgroup per tile in queue order for LDS tiles, a persistent
 // grid popping tiles with an atomic counter for global-scratch tiles.  The
@@ -19,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <new>
 #include <string>
 #include <vector>
@@ -30,11 +32,6 @@ namespace mf {
 
 constexpr int kMaxItems = 33;  // register capacity allowed to batch plans (as plain)
 constexpr int kLanes = 4;      // streams a launch spreads its groups over
-
-// Descriptors are read through the constant address space, so the tile body
-// loads each field with a scalar load where it is used, as it does a kernel
-// argument, instead of holding a copy in registers.
-using ConstDesc = const __attribute__((address_space(4))) ImageDesc;
 
 // Register-capacity (LDS) groups: one workgroup per tile of the slice, in
 // queue order, so the longest tiles are dispatched first.
@@ -87,8 +84,7 @@ __global__ __launch_bounds__(kThreads) void mf_batched_gs_kernel(ConstDesc* desc
 
 namespace {
 
-using BatchFn = void (*)(ConstDesc*, const int2*, int, int, int*, unsigned char*,
-                         long long);
+using BatchFn = BatchKernelFn;
 
 // Kernel variant of a planned image: 0..3 = register capacity 9/17/25/33,
 // 4 = global scratch.
@@ -117,6 +113,12 @@ BatchFn pick_batched(int kt, int shape, int v) {
                              : pick_batched_variant<KEY_F32, SHAPE_SPANS>(v);
 }
 
+BatchFn pick_batched_bits(const ImageDesc& d) {
+  const int v = d.bits - 1;
+  return d.kt == MF_U8 ? pick_bits_batched_u8(v) : d.kt == MF_U16 ? pick_bits_batched_u16(v)
+                                                                  : pick_bits_batched_f32(v);
+}
+
 // Relative tile cost for longest-first ordering: sort work over the box plus
 // slide and scan work over the tile's pixels.
 double tile_cost(const ImageDesc& d) {
@@ -124,6 +126,10 @@ double tile_cost(const ImageDesc& d) {
   return (double)d.T * passes * 4.0 + (double)d.tw * d.th * (2.0 * d.ncols + 160.0) +
          (d.gs ? (double)d.T * passes * 8.0 : 0.0);
 }
+
+// tile_cost of a tile that takes a compute unit one microsecond (disc 32
+// uint16, 64 x 64 tiles: 1.45 M, 78 us), for bit-plane tiles.
+constexpr double kCostPerUs = 18600.0;
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
@@ -138,6 +144,7 @@ struct BatchGroup {
   BatchFn fn = nullptr;
   int begin = 0, end = 0;   // queue slice
   int grid = 0;
+  int threads = kThreads;
   int lds_bytes = 0;
   long long slot_bytes = 0;
   long long scratch_off = 0;
@@ -228,6 +235,12 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
     int2 it;
   };
   std::vector<Item> items;
+  // Windows that the bit planes take run on them here too, by the rule of a
+  // plain call on an image of the whole batch's pixels: that is the work the
+  // chip has, so one footprint takes one variant whatever the sizes.
+  double px = 0;
+  for (int i = 0; i < n; ++i) px += (double)descs[i].w * (double)descs[i].h;
+  const int side = (int)std::min(32768.0, std::ceil(std::sqrt(px)));
   for (int i = 0; i < n; ++i) {
     const mf_image_desc& e = descs[i];
     if (!e.w || !e.h) {
@@ -235,16 +248,20 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
       continue;
     }
     const void* table = nullptr;
+    double us = 0;
     if ((rc = footprint_device_table(e.fp, dev, &table, nullptr)) ||
-        (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i]))) {
+        (bits_plan(e.dtype, e.fp, di.lds_max, side, side, di.cus, &hd[i], &us) != MF_OK &&
+         (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i])))) {
       mf_plan_destroy(p);
       return rc;
     }
     bind_image(&hd[i], e.img, e.w, e.h, e.stride_bytes, e.dtype, e.fp, e.boundary,
                (e.fp->taps - 1) / 2, table);
     hd[i].out = e.out;
-    const int key = (hd[i].kt * 2 + hd[i].shape) * 5 + variant_of(hd[i]);
-    const double c = tile_cost(hd[i]);
+    const int key = hd[i].bits ? 30 + hd[i].kt * kBitsVariants + hd[i].bits
+                               : (hd[i].kt * 2 + hd[i].shape) * 5 + variant_of(hd[i]);
+    const double c = hd[i].bits ? kCostPerUs * us * di.cus / (px / ((double)hd[i].tw * hd[i].th))
+                                : tile_cost(hd[i]);
     const int nt = hd[i].tiles_x * hd[i].tiles_y;
     for (int t = 0; t < nt; ++t) items.push_back({key, c, make_int2(i, t)});
   }
@@ -259,7 +276,8 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
     size_t j = i;
     BatchGroup g;
     const ImageDesc& d0 = hd[items[i].it.x];
-    g.fn = pick_batched(d0.kt, d0.shape, variant_of(d0));
+    g.fn = d0.bits ? pick_batched_bits(d0) : pick_batched(d0.kt, d0.shape, variant_of(d0));
+    if (d0.bits) g.threads = bits_threads(d0.bits - 1);
     for (; j < items.size() && items[j].key == items[i].key; ++j) {
       const ImageDesc& d = hd[items[j].it.x];
       g.lds_bytes = std::max(g.lds_bytes, d.lds_bytes);
@@ -340,7 +358,7 @@ int mf_plan_launch(mf_plan* p, hipStream_t stream) {
   for (size_t i = 0; i < p->groups.size(); ++i) {
     const mf::BatchGroup& g = p->groups[i];
     hipStream_t s = g.lane ? p->side[g.lane - 1] : stream;
-    hipLaunchKernelGGL(g.fn, dim3(g.grid), dim3(mf::kThreads), g.lds_bytes, s,
+    hipLaunchKernelGGL(g.fn, dim3(g.grid), dim3(g.threads), g.lds_bytes, s,
                        (mf::ConstDesc*)p->d_descs, p->d_queue, g.begin, g.end, p->d_counters + 2 * i,
                        g.slot_bytes ? p->d_scratch + g.scratch_off : nullptr, g.slot_bytes);
     if (hipGetLastError() != hipSuccess) rc = MF_ERR_HIP;

@@ -207,6 +207,19 @@ int median_filter_ranks(const void* img, int w, int h, size_t stride_bytes, int 
   const void* table = nullptr;
   if ((rc = footprint_device_table(fp, dev, &table, stream))) return rc;
   ImageDesc a{};
+  // Constant ranks of a window the bit planes take: a launch per plane, each
+  // as fast as a plain call (a plane of the shared tiles takes as long as a
+  // plain tile call or longer, its sort apart).
+  bool maps = false;
+  for (int q = 0; q < nouts; ++q) maps = maps || outs[q].rank_map;
+  if (!maps && bits_plan(dtype, fp, di.lds_max, w, h, di.cus, &a) == MF_OK) {
+    for (int q = 0; q < nouts; ++q) {
+      bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, outs[q].rank, table);
+      a.out = outs[q].out;
+      if ((rc = launch_bits(a, stream))) return rc;
+    }
+    return MF_OK;
+  }
   if ((rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus))) return rc;
   bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, (fp->taps - 1) / 2, table);
   a.out = outs[0].out;
@@ -268,22 +281,33 @@ int median_filter_windows(const void* img, int w, int h, size_t stride_bytes, in
   // float32 disc 48 + ellipse 60x20 + hexagon R=40 set in one pass (1.19x
   // at 3840x2160).
   constexpr double kFuse = 0.25;
+  const bool fuse_all = window_fusion_all();
   int order[MF_MAX_RANK_OUTPUTS];
+  int left = 0, alone = 0;   // windows of the passes (from the front), others (from the back)
   long long boxT[MF_MAX_RANK_OUTPUTS];
   double gain[MF_MAX_RANK_OUTPUTS];
   for (int q = 0; q < nouts; ++q) {
     ImageDesc p{};
+    // a window the bit planes take is cheaper alone than as a plane of a pass
+    if (!fuse_all && !outs[q].rank_map &&
+        bits_plan(dtype, outs[q].footprint, di.lds_max, w, h, di.cus, &p) == MF_OK) {
+      order[nouts - ++alone] = q;
+      continue;
+    }
     if ((rc = choose_plan(dtype, outs[q].footprint, di.lds_max, 33, &p, w, h, di.cus, false))) return rc;
     boxT[q] = p.T;
     gain[q] = (double)p.T / ((double)p.tw * p.th) * (double)outs[q].footprint->taps;
-    order[q] = q;
+    order[left++] = q;
   }
-  std::stable_sort(order, order + nouts, [&](int x, int y) { return boxT[x] > boxT[y]; });
-  const bool fuse_all = window_fusion_all();
-  for (int g0 = 0; g0 < nouts;) {
+  std::stable_sort(order, order + left, [&](int x, int y) { return boxT[x] > boxT[y]; });
+  for (int i = nouts - 1; i >= left; --i)
+    if ((rc = launch_window_pass(img, w, h, stride_bytes, dtype, boundary, outs, order + i, 1, dev,
+                                 di, stream)))
+      return rc;
+  for (int g0 = 0; g0 < left;) {
     const long long t0 = boxT[order[g0]];
     int g1 = g0 + 1;
-    while (g1 < nouts &&
+    while (g1 < left &&
            (fuse_all || gain[order[g1]] >= kFuse * (double)(t0 - boxT[order[g1]])))
       ++g1;
     if ((rc = launch_window_pass(img, w, h, stride_bytes, dtype, boundary, outs, order + g0,

@@ -207,11 +207,21 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
 PlainKernelFn pick_general_kernel(const ImageDesc& d);
 // Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
 // kernel, and launch with a complete plan.
-int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d);
+// us (optional): the estimated time of the image.
+int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d,
+              double* us = nullptr);
 PlainKernelFn pick_bits_u8(int v);
 PlainKernelFn pick_bits_u16(int v);
 PlainKernelFn pick_bits_f32(int v);
 int bits_threads(int v);
+// Kernels of batch plans: descriptors (read through the constant address
+// space, so that each field is a scalar load where it is used instead of a
+// copy in registers), tile queue, slice [begin, end), counters and scratch.
+using ConstDesc = const __attribute__((address_space(4))) ImageDesc;
+using BatchKernelFn = void (*)(ConstDesc*, const int2*, int, int, int*, unsigned char*, long long);
+BatchKernelFn pick_bits_batched_u8(int v);
+BatchKernelFn pick_bits_batched_u16(int v);
+BatchKernelFn pick_bits_batched_f32(int v);
 int launch_bits(const ImageDesc& a, hipStream_t stream);
 // median_filter_windows: one pass for all windows (set by
 // mf_set_window_fusion) instead of grouping them by box size.
