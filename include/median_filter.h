@@ -414,8 +414,9 @@ int mf_plan_autotune(const mf_image_desc* descs, int n, hipStream_t stream, int 
 int mf_tune_cache_load(const char* path);
 int mf_tune_cache_save(const char* path);
 
-/* The tile shape and launch of the tile engine for this image and footprint
- * (calls that run on bit planes instead have a tile of their own): output
+/* The tile engine's shape for this image and footprint: an override, a tuned
+ * shape or the default one, which a call may still fit to few tiles or to a
+ * large window (calls that run on bit planes have a tile of their own): output
  * tile size, input box size (tile + window extent) and the LDS bytes per
  * workgroup.  Host-only; runs no GPU code. */
 int mf_query_plan(int w, int h, int dtype, const mf_footprint* fp, int* tile_w, int* tile_h,

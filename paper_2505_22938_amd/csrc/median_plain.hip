@@ -209,7 +209,7 @@ int query_plan(int w, int h, int dtype, const mf_footprint* fp, ImageDesc* d) {
     di.lds_max = 160 * 1024;
     di.cus = 256;
   }
-  return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus);
+  return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus, false);
 }
 
 int set_counters(int enable) {

@@ -109,7 +109,8 @@ struct ImageDesc {
   unsigned char* scratch;
   long long slot_bytes;
   unsigned int* claim;
-  int off_x1, off_lr, ipt;
+  // off_sort: LDS offset of the digit counters of float keys sorted in LDS
+  int off_x1, off_sort, ipt;
   // kernel selection: key type, shape, 1 = global-scratch variant, and the
   // register capacity (elements per thread) of the LDS variant
   int kt, shape, gs, imax;
@@ -152,9 +153,10 @@ int device_info(int dev, DeviceInfo* out);
 int make_plan(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, ImageDesc* d);
 int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, ImageDesc* d);
 // w, h, cus (image size and compute units, 0 = unknown) let the default
-// choice keep enough tiles per CU and, with `spread`, take the shape that
-// suits a small image (plan_us: its estimated time).  choose_plan_tall: the override or the
-// tallest default shape, ignoring the tuned table (bracketed tiles).
+// choice keep enough tiles per CU; with `spread` it is fitted to the call
+// (fit_plan, and for small images by plan_us, a shape's estimated time).
+// choose_plan_tall: the override or the tallest default shape, ignoring the
+// tuned table (bracketed tiles).
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
                 int w = 0, int h = 0, int cus = 0, bool spread = true);
 double plan_us(const ImageDesc& c, int w, int h, int cus);

@@ -129,7 +129,7 @@ int make_plan(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, Im
   d->gs = 0;
   d->imax = im;
   d->slot_bytes = 0;
-  d->off_x1 = d->off_lr = d->ipt = 0;
+  d->off_x1 = d->off_sort = d->ipt = 0;
   if (d->lds_bytes > lds_max) return MF_ERR_UNSUPPORTED;
   return MF_OK;
 }
@@ -171,7 +171,7 @@ int make_plan_br(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
   const int need_items = ((T + kThreads - 1) / kThreads) | 1;
   d->imax = need_items <= 9 ? 9 : need_items <= 17 ? 17 : need_items <= 25 ? 25 : 0;
   d->slot_bytes = 0;
-  d->off_x1 = d->off_lr = d->ipt = 0;
+  d->off_x1 = d->off_sort = d->ipt = 0;
   d->br_cap = cap;
   if (d->lds_bytes > lds_max) return MF_ERR_UNSUPPORTED;
   return MF_OK;
@@ -191,11 +191,23 @@ int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
   // over x0.  The output is read back from the image (no reverse map).
   // Region B also holds the sort's packed 16-bit key counters (2^16 of
   // them for 16-bit and float keys, 2^8 for 8-bit keys).
-  const int B = std::max(B0, dtype == MF_U8 ? 512 : 131072);
+  int B = std::max(B0, dtype == MF_U8 ? 512 : 131072);
+  // float keys whose words fit LDS are sorted there (up to 38 thousand of
+  // them: disc 48 in 64 x 128 tiles); the digit counters lie behind the words
+  // and, in the last pass, behind the ordinal image and the omnigram
+  d->off_sort = 0;
+  if (dtype == MF_F32) {
+    const int words = std::max(4 * TP, ib + 2 * TP);
+    const int Bs = std::max(B, words + round_up(2 * kWaves * 258, 16));
+    const int chunks = (d->bw + 3) / 4 * d->bh;   // of four words, ten to a thread
+    if (chunks <= 10 * kThreads && Bs + table_bytes(d) <= lds_max - 256) {
+      d->off_sort = words;
+      B = Bs;
+    }
+  }
   d->off_p = 0;
   d->off_C = 0;
   d->off_x1 = 4 * TP;
-  d->off_lr = 0;
   d->slot_bytes = round_up(dtype == MF_F32 ? 8 * TP : 2 * TP, 256);
   d->ipt = (T + kThreads - 1) / kThreads;
   d->off_B = 0;
@@ -222,6 +234,11 @@ static int plan_shape(int dtype, const mf_footprint* fp, int lds_max, int imax_c
   return make_plan_gs(dtype, fp, lds_max, tw, th, d);
 }
 
+// Weight of a box pixel of float keys sorted in global scratch against one
+// sorted in LDS (3840 x 2160: disc 56, 64x128 tiles sorted in global scratch
+// 1.67 ms, 64x96 in LDS 1.18; disc 64, 64x96 2.12, 54x80 in LDS 1.59).
+constexpr double kGlobalSort = 1.6;
+
 // Global-scratch plans (large windows): the tile shape with the least box
 // amplification T / (tw * th) among shapes that keep at least 3/4 of the
 // lanes and half of the waves busy in the band phase.  Widths need not
@@ -240,7 +257,8 @@ int best_gs_plan(int dtype, const mf_footprint* fp, int lds_max, ImageDesc* d) {
       if (make_plan_gs(dtype, fp, lds_max, w, h, &c) != MF_OK) continue;
       const int bands = (h + c.band_rows - 1) / c.band_rows;
       if (bands * 2 < kWaves * segs && h > kWaves) continue;
-      const double amp = (double)c.T / ((double)w * h);
+      const double amp = (double)c.T / ((double)w * h) *
+                         (dtype == MF_F32 && !c.off_sort ? kGlobalSort : 1.0);
       if (amp < best) {
         best = amp;
         pick = c;
@@ -272,7 +290,8 @@ static int default_th_cap(const mf_footprint* fp) {
 // The first LDS shape that fits (widest, then tallest first, heights up to
 // th_cap), unless a global-scratch shape re-reads enough fewer box pixels
 // per output pixel (small LDS tiles under large windows).  Measured
-// crossover, as the ratio of the LDS plan's amplification to the
+// crossover, with the sort scattered in global scratch (fit_plan moves it for
+// the sort in LDS), as the ratio of the LDS plan's amplification to the
 // global-scratch plan's: about 1.25 for 8/16-bit keys (4096^2 uint16 disc:
 // radius 48, ratio 1.14, 1.91 ms in LDS against 2.06; radius 52, 1.27,
 // 2.22 against 2.19; radius 56, 1.47, 2.56 against 2.33; radius 60, 3.15
@@ -349,11 +368,47 @@ static int default_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
 double plan_us(const ImageDesc& c, int w, int h, int cus) {
   const bool f32 = c.kt == MF_F32;
   const double fixed = f32 ? 30.0 : 22.0;
-  const double key = f32 ? (c.gs ? 6.0 : 3.4) : (c.gs ? 2.6 : 2.2);
+  const double key = f32 ? (c.gs && !c.off_sort ? 6.0 : 3.4) : 2.2;
   const double walk = (f32 ? 0.5 : 0.9) * 64.0 / (c.tw * c.segs);
   const double T = c.T * 1e-3, px = c.tw * c.th * 1e-3;
   const long long tiles = (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
   return (fixed + key * T + walk * T * px) * (double)((tiles + cus - 1) / cus);
+}
+
+// The default shape fitted to the call (w, h, cus as choose_plan's).
+// A window past radius 16 in an LDS shape takes the global-scratch shape of
+// least amplification from a ratio of 1.05 on where its sort stays in LDS
+// (4096^2 uint16 smooth: radius 40, both 64x128, 1.46 ms; radius 44, ratio
+// 1.06, 1.54 in LDS against 1.46; radius 48, 1.14, 1.69 against 1.54;
+// 3840x2160 float32: radius 32, 1.11, 0.79 against 0.76; radius 40, 1.38,
+// 0.97 against 0.84; radius 44, 1.68, 1.25 against 0.88).  The ratio is that
+// of the tallest LDS shape, and the image has to give about two tiles per CU
+// (2048^2 uint16 radius 48, 512 tiles, 0.57 in 64x64 LDS tiles against 0.54
+// smooth, 0.46 against 0.37 noise; 1500x1200, 240 tiles, 0.28 against 0.34).
+// A window of radius 24 (float keys: 20) and more whose LDS shape stepped down to 64x64 for
+// four tiles per CU takes 64x96 where it gives 2.6 (2048 x 2048, 704 tiles:
+// uint16 smooth disc 24 / 32 / 48 361 / 416 / 573 -> 328 / 384 / 519 us,
+// float32 disc 20 / 24 / 32 383 / 390 / 436 -> 352 / 360 / 432; uint16 disc 20
+// 300 against 308 and on noise 276 against 297).
+static void fit_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h,
+                     int cus, ImageDesc* d) {
+  const bool sized = w > 0 && h > 0 && cus > 0;
+  auto tiles = [&](const ImageDesc& c) {
+    return (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
+  };
+  if (d->gs || std::min(d->nrows, d->ncols) <= 33) return;
+  ImageDesc c{}, tall{};
+  if (best_gs_plan(dtype, fp, lds_max, &c) == MF_OK && (dtype != MF_F32 || c.off_sort) &&
+      default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), 0, 0, 0, &tall) == MF_OK &&
+      (double)tall.T * c.tw * c.th > 1.05 * (double)c.T * tall.tw * tall.th &&
+      (!sized || tiles(c) * 10 >= 19LL * cus)) {
+    *d = c;
+    return;
+  }
+  if (sized && d->tw == 64 && d->th == 64 && std::min(d->nrows, d->ncols) > (dtype == MF_F32 ? 40 : 46) &&
+      make_plan(dtype, fp, lds_max, 64, 96, &c) == MF_OK && c.imax <= imax_cap &&
+      tiles(c) * 10 >= 26LL * cus)
+    *d = c;
 }
 
 // Images of fewer than about four tiles per CU: the shape whose rounds of
@@ -397,7 +452,10 @@ int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, Im
   const bool sized = w > 0 && h > 0 && cus > 0;
   const int rc = default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), w, h,
                               sized ? 4LL * cus : 0, d);
-  if (rc == MF_OK && sized && spread) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+  if (rc == MF_OK && spread) {
+    fit_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+    if (sized) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+  }
   return rc;
 }
 

@@ -73,12 +73,15 @@ __device__ __forceinline__ uint32_t key_to_f32(uint32_t k) {
   return k ^ (((k >> 31) - 1u) | 0x80000000u);
 }
 
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(v, d, 64);
-    if (lane >= d) v += o;
-  }
+// (DPP moves inside rows of 16 lanes, then the last lane of each row, and of
+// each half, to the rows after it: no LDS traffic)
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31
   return v;
 }
 
@@ -352,33 +355,115 @@ __device__ __forceinline__ void global_radix_sort(uint32_t* xa, uint32_t* xb, in
   }
 }
 
-// Exclusive scan, in place, over the 2 * nw 16-bit counters packed two per
-// word in w (counter 2i in the low half of word i); the totals stay below
-// 65536.  Wave v owns the contiguous run of words [v * per, (v + 1) * per)
-// and walks it 64 words at a time, lane l on word l of each step, so every
-// LDS access of a step falls in its own bank (a run per thread would put
-// all lanes of a wave on two banks).  Contains barriers.
-__device__ __forceinline__ void packed_exclusive_scan(uint32_t* w, int nw, uint32_t* wsum) {
+// The two stable 8-bit passes over the high halves of T words in LDS (key
+// bits << 16 | location), in place: a pass holds all words in registers while
+// it writes them back.  out(word, o) receives each word with its final
+// position instead of the last write.  Waves own contiguous elements as in
+// global_radix_sort; ITEMS * kThreads >= T.  An element's rank among the equal
+// digits of its wave is found as the wave counts (the counter before its step
+// plus its rank in the step), so a pass needs the ballots once and no
+// atomics.  Counters: cw[wave * 258 + digit], 16 bits.
+template <int ITEMS, typename F>
+__device__ __forceinline__ void lds_radix_sort(uint32_t* x, int T, uint16_t* cw, uint32_t* wsum,
+                                               F&& out) {
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  constexpr int kPitch = 258;
+  const int S = (((T + kWaves - 1) / kWaves) + 63) & ~63;
+  const int e0 = wid * S, e1 = min(e0 + S, T);
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint16_t* mine = cw + wid * kPitch;
+  for (int pass = 0; pass < 2; ++pass) {
+    const int sh = 16 + 8 * pass;
+    uint32_t w[ITEMS], r2[ITEMS / 2];
+    for (int i = t; i < kWaves * kPitch / 2; i += kThreads) reinterpret_cast<uint32_t*>(cw)[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (e0 + 64 * i < e1) {
+        const int e = e0 + 64 * i + lane;
+        const bool valid = e < e1;
+        w[i] = valid ? x[e] : 0u;
+        const uint32_t d = (w[i] >> sh) & 255u;
+        const uint64_t peers = digit_peers8(d, valid);
+        const uint32_t base = mine[d];
+        const uint32_t r = base + (uint32_t)__popcll(peers & lt);
+        r2[i / 2] = i % 2 ? r2[i / 2] | (r << 16) : r;
+        if (valid && (peers & ~lt) == (1ull << lane))
+          mine[d] = (uint16_t)(base + (uint32_t)__popcll(peers));
+      }
+    __syncthreads();
+    {
+      // thread t scans entries 4t .. 4t + 3 of the digit-major order
+      const int d = t >> 2, w0 = (t & 3) * 4;
+      uint32_t c[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = cw[(w0 + j) * kPitch + d];
+      uint32_t b = block_exclusive_scan(c[0] + c[1] + c[2] + c[3], wsum);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        cw[(w0 + j) * kPitch + d] = (uint16_t)b;
+        b += c[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (e0 + 64 * i < e1 && e0 + 64 * i + lane < e1) {
+        const uint32_t o = mine[(w[i] >> sh) & 255u] + ((r2[i / 2] >> (i % 2 * 16)) & 0xffffu);
+        if (pass == 0) x[o] = w[i];
+        else out(w[i], o);
+      }
+    __syncthreads();
+  }
+}
+
+// Exclusive scan, in place, over the 16-bit counters packed two per word in
+// NQ * 4 * kThreads words at w (the lower half first); the totals stay below
+// 65536.  Wave v owns NQ runs of 256 words side by side, four words to a lane
+// and all in registers, so the words cross the LDS once each way in 16-byte
+// accesses.  Contains barriers.
+template <int NQ>
+__device__ __forceinline__ void packed_exclusive_scan(uint32_t* w, uint32_t* wsum) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int per = (nw + kWaves - 1) / kWaves;
-  const int w0 = wid * per, w1 = min(w0 + per, nw);
-  uint32_t sum = 0;
-  for (int i = w0 + lane; i < w1; i += 64) {
-    const uint32_t v = w[i];
-    sum += (v & 0xffffu) + (v >> 16);
+  uint4* row = reinterpret_cast<uint4*>(w) + wid * NQ * 64 + lane;
+  uint4 q[NQ];
+  uint32_t incl[NQ], tot = 0;
+#pragma unroll
+  for (int s = 0; s < NQ; ++s) q[s] = row[64 * s];
+  auto halves = [](uint32_t v) { return (v & 0xffffu) + (v >> 16); };
+#pragma unroll
+  for (int s = 0; s < NQ; ++s) {
+    const uint32_t sum = halves(q[s].x) + halves(q[s].y) + halves(q[s].z) + halves(q[s].w);
+    const uint32_t in = wave_inclusive_scan(sum, lane);
+    incl[s] = tot + in - sum;   // (exclusive, in the wave's run)
+    tot += (uint32_t)__builtin_amdgcn_readlane((int)in, 63);
   }
-  // the runs before this wave's: the exclusive prefix of one value per wave
-  const uint32_t tot = __shfl(wave_inclusive_scan(sum, lane), 63, 64);
-  uint32_t run = block_exclusive_scan(lane == 63 ? tot : 0u, wsum);
-  for (int i0 = w0; i0 < w1; i0 += 64) {
-    const int i = i0 + lane;
-    const uint32_t v = i < w1 ? w[i] : 0u;
-    const uint32_t lo = v & 0xffffu, s = lo + (v >> 16);
-    const uint32_t incl = wave_inclusive_scan(s, lane);
-    const uint32_t b = run + incl - s;
-    if (i < w1) w[i] = b | ((b + lo) << 16);
-    run += __shfl(incl, 63, 64);
+  if (lane == 0) wsum[wid] = tot;
+  __syncthreads();
+  uint32_t pre = 0;
+  for (int j = 0; j < wid; ++j) pre += wsum[j];
+#pragma unroll
+  for (int s = 0; s < NQ; ++s) {
+    uint32_t b = pre + incl[s];
+    auto put = [&](uint32_t v) {
+      const uint32_t lo = b, hi = b + (v & 0xffffu);
+      b = hi + (v >> 16);
+      return lo | (hi << 16);
+    };
+    q[s].x = put(q[s].x);
+    q[s].y = put(q[s].y);
+    q[s].z = put(q[s].z);
+    q[s].w = put(q[s].w);
+    row[64 * s] = q[s];
   }
+}
+
+// The same over the 128 words of the 8-bit keys' counters.
+__device__ __forceinline__ void packed_exclusive_scan_u8(uint32_t* w, uint32_t* wsum) {
+  const int t = threadIdx.x;
+  const uint32_t v = t < 128 ? w[t] : 0u;
+  const uint32_t b = block_exclusive_scan((v & 0xffffu) + (v >> 16), wsum);
+  if (t < 128) w[t] = b | ((b + (v & 0xffffu)) << 16);
 }
 
 }  // namespace mf

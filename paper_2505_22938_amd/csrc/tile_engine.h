@@ -11,23 +11,26 @@
 //           their ordinals in any order), then stable 4-bit LSD passes
 //   I       ordinal image, I(loc(v)) = v, 16-bit, row pitch chosen so rows
 //           start in different LDS banks
-//   bands   the tile is cut into bands of `band_rows` rows (the last one
-//           may be shorter) and each wave owns `segs` = 64 / tw bands side
-//           by side (a band is tw <= 64 columns, one lane per column; lanes
-//           past segs * tw and bands past the tile sit out).  Per band:
-//             seeds the band's first row is cut into chunks of 16 columns;
-//                   the first chunk's window is solved with a coarse
+//   bands   the tile is cut into bands of 2 * `band_rows` rows (the last one
+//           may be shorter) and each pair of waves owns `segs` = 64 / tw bands
+//           side by side (a band is tw <= 64 columns, one lane per column;
+//           lanes past segs * tw and bands past the tile sit out); chained
+//           tiles: bands of `band_rows` rows, one wave each.  Per band:
+//             seeds the band's middle row (chained: first) is cut into chunks
+//                   of 8 columns (16), shared by the two waves; a wave's
+//                   first chunk is solved with a coarse
 //                   histogram of its ordinals refined by an omnigram scan
 //                   (paper: seeds solved from low-precision histograms, then
 //                   refined), each later chunk's by moving the previous
-//                   chunk's window 16 columns right;
+//                   chunk's window on;
 //             row   the four 16-lane rows of the wave take one chunk each
 //                   and slide their windows right one pixel at a time in
 //                   lockstep (paper: short horizontal slides from many
 //                   seeds), counting entering and leaving pixels against
 //                   the pivot across the row's lanes and refining by a
 //                   row-wide omnigram scan;
-//             sweep every lane then slides its window down the band: count
+//             sweep one wave of the pair slides up from that row, the other
+//                   (or the only one) down, every lane its own window: count
 //                   += #entering < pivot - #leaving < pivot over the window's
 //                   columns (adjacent lanes read adjacent pixels), then each
 //                   lane walks the omnigram for its window's new median;
@@ -1185,116 +1188,292 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
    }
   } else {
     // One counting pass over the low 16 bits of the key (8-bit keys: all
-    // 8): box pixels are counted per key value straight from the image by
-    // LDS atomics on packed 16-bit counters, the counters are scanned, and
-    // each pixel is read again and claims the next slot of its key value.
-    // Ties take their slots in any order, which the ordinal transform
-    // allows, so 8/16-bit keys are fully sorted: each slot receives just
-    // the pixel's location, the omnigram entry (the output is read back
-    // from the image, so no reverse map is kept).  Float keys go to x0 as
-    // (high 16 key bits << 16 | location) words for two stable 8-bit
-    // passes over the high bits.
-    uint32_t* x0 = reinterpret_cast<uint32_t*>(gslot);
-    uint32_t* x1 = reinterpret_cast<uint32_t*>(gslot + a.off_x1);
+    // 8): the box is read into registers and counted per key value by LDS
+    // atomics on packed 16-bit counters, the counters are scanned, and each
+    // element claims the next slot of its key value.  Ties take their slots
+    // in any order, which the ordinal transform allows, so 8/16-bit keys are
+    // fully sorted and an element's slot, kept in place of its key, is its
+    // ordinal.  The counters then make room: the omnigram is scattered into
+    // LDS, copied to the slot in whole lines, and the ordinal image is
+    // written from the registers.  (A scatter straight to the slots writes
+    // two bytes to a line at a time, 130 KB for each of 32 workgroups on a
+    // 4 MB L2: 2 to 3 GB went to memory on 4096 x 4096.)  Float keys go on
+    // as (high 16 key bits << 16 | location) words for two stable 8-bit
+    // passes over the high bits, in LDS where the words fit (a.off_sort: the
+    // passes' digit counters), else in the slot (x0, x1).
+    // 4096 x 4096 uint16 disc 100 5.87 -> 4.87 ms (the sort 348 -> 211 thousand
+    // clocks of a tile), 3840 x 2160 float32 disc 48 1.42 -> 0.85 (519 -> 233).
     uint32_t* pcnt = reinterpret_cast<uint32_t*>(cnt);
+    uint16_t* om_lds = reinterpret_cast<uint16_t*>(smem);
     constexpr int KB = KT == KEY_U8 ? 8 : 16;
     constexpr int NW = 1 << (KB - 1);   // counter words, two counters each
-    // Both passes read the box kGB elements per thread at a time (element
-    // e = e0 + j * kThreads + t, coordinates stepped as in the LDS load), the
-    // loads of a batch in flight together, then apply the batch's atomics.
-    constexpr int kGB = 8;
-    const int sx = kThreads % a.bw, sy = kThreads / a.bw;
-    auto load_batch = [&](int e0, int& lx, int& ly, uint32_t (&kk)[kGB], uint32_t (&ll)[kGB]) {
+    // Registers hold chunks of 16 bytes of a box row (thread t: chunks t, t +
+    // kThreads, .. in row order), all loads in flight together; chunks across
+    // the image's edge are read again pixel by pixel.
+    using E = typename std::conditional<
+        KT == KEY_U8, uint8_t,
+        typename std::conditional<KT == KEY_U16, uint16_t, uint32_t>::type>::type;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef u32x4 u32x4_any __attribute__((aligned(1)));
+    constexpr int EC = 16 / (int)sizeof(E);
+    constexpr int NB = KT == KEY_U8 ? 4 : KT == KEY_U16 ? 8 : 10;
+    const int cpr = (a.bw + EC - 1) / EC, nch = cpr * a.bh;
+    // f(b, x, y, live) of this thread's chunks in order
+    auto chunks = [&](auto&& f) {
+      int tt = t;
+      asm volatile("" : "+v"(tt));   // coordinates anew in each phase: kept, they would spill
+      int cx = tt % cpr, cy = tt / cpr;
+      const int sx = kThreads % cpr, sy = kThreads / cpr;
 #pragma unroll
-      for (int j = 0; j < kGB; ++j) {
-        // unconditional (remap keeps coordinates inside the image); elements
-        // numbered >= T are not used
-        const int gx = remap(gx0 + lx, a.w, a.boundary);
-        const int gy = remap(gy0 + ly, a.h, a.boundary);
-        const long long off = (long long)gy * a.stride + gx;
-        ll[j] = (uint32_t)((ly << 8) | lx);
-        if (KT == KEY_U8) kk[j] = static_cast<const uint8_t*>(a.img)[off];
-        if (KT == KEY_U16) kk[j] = static_cast<const uint16_t*>(a.img)[off];
-        if (KT == KEY_F32) kk[j] = f32_to_key(static_cast<const uint32_t*>(a.img)[off]);
-        if (corner_cut(lx, ly)) kk[j] = kTopKey;
-        lx += sx;
-        ly += sy;
-        if (lx >= a.bw) {
-          lx -= a.bw;
-          ly += 1;
+      for (int b = 0; b < NB; ++b) {
+        if (b * kThreads < nch) f(b, cx * EC, cy, b * kThreads + tt < nch);
+        __builtin_amdgcn_sched_barrier(0);
+        cx += sx;
+        cy += sy;
+        if (cx >= cpr) {
+          cx -= cpr;
+          cy += 1;
         }
       }
-      (void)e0;
     };
-    for (int b = t; b < NW; b += kThreads) pcnt[b] = 0;
-    __syncthreads();
-    {
-      int lx = t % a.bw, ly = t / a.bw;
-      for (int e0 = 0; e0 < T; e0 += kGB * kThreads) {
-        uint32_t kk[kGB], ll[kGB];
-        load_batch(e0, lx, ly, kk, ll);
+    auto load_box = [&](u32x4 (&v)[NB]) {
+      const E* img = static_cast<const E*>(a.img);
+      if (a.w >= EC)
+        chunks([&](int b, int x, int y, bool) {
+          const int gy = remap(gy0 + min(y, a.bh - 1), a.h, a.boundary);
+          v[b] = *reinterpret_cast<const u32x4_any*>(img + (long long)gy * a.stride +
+                                                     min(max(gx0 + x, 0), a.w - EC));
+        });
+      chunks([&](int b, int x, int y, bool) {
+        if (gx0 + x >= 0 && gx0 + x + EC <= a.w) return;
+        const E* row = img + (long long)remap(gy0 + min(y, a.bh - 1), a.h, a.boundary) * a.stride;
+        v[b] = u32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int j = 0; j < kGB; ++j)
-          if (e0 + j * kThreads + t < T) {
-            const uint32_t d = kk[j] & ((1u << KB) - 1u);
-            atomicAdd(&pcnt[d >> 1], 1u << ((d & 1u) << 4));
+        for (int j = 0; j < EC; ++j)
+          v[b][j * (int)sizeof(E) / 4] |=
+              (uint32_t)row[remap(gx0 + min(x + j, a.bw - 1), a.w, a.boundary)]
+              << (8 * (j * (int)sizeof(E) % 4));
+      });
+    };
+    // corners of the box outside every window: the distance from the centres
+    // is convex along a chunk, so its ends tell
+    auto chunk_cut = [&](int x, int y) {
+      return cut && (corner_cut(x, y) || corner_cut(x + EC - 1, y));
+    };
+    auto count = [&](uint32_t k) {
+      const uint32_t d = k & ((1u << KB) - 1u);
+      atomicAdd(&pcnt[d >> 1], 1u << ((d & 1u) << 4));
+    };
+    auto claim = [&](uint32_t k) {
+      const uint32_t d = k & ((1u << KB) - 1u), sh = (d & 1u) << 4;
+      return (atomicAdd(&pcnt[d >> 1], 1u << sh) >> sh) & 0xffffu;
+    };
+    auto clear_counters = [&] {
+      if constexpr (KT == KEY_U8) {
+        if (t < NW) pcnt[t] = 0;
+      } else {
+#pragma unroll
+        for (int i = 0; i < NW / 4 / kThreads; ++i)
+          reinterpret_cast<uint4*>(pcnt)[i * kThreads + t] = make_uint4(0, 0, 0, 0);
+      }
+    };
+    auto scan_counters = [&] {
+      if constexpr (KT == KEY_U8) packed_exclusive_scan_u8(pcnt, wsum);
+      else packed_exclusive_scan<NW / 4 / kThreads>(pcnt, wsum);
+    };
+    // the omnigram from LDS to the slot (its padding is written below)
+    auto copy_om = [&](const uint16_t* from) {
+      const uint4* src = reinterpret_cast<const uint4*>(from);
+      uint4* dst = reinterpret_cast<uint4*>(om);
+      for (int i = t; i < (T + 7) / 8; i += kThreads) dst[i] = src[i];
+    };
+    if constexpr (KT != KEY_F32) {
+      uint32_t kv[NB * EC / 2];   // keys, then slots: two elements a word
+      {
+        u32x4 v[NB];
+        load_box(v);
+        clear_counters();
+        __syncthreads();
+        chunks([&](int b, int x, int y, bool live) {
+#pragma unroll
+          for (int q = 0; q < EC / 2; ++q)
+            kv[b * (EC / 2) + q] =
+                KT == KEY_U16 ? v[b][q % 4]
+                              : __builtin_amdgcn_perm(0, v[b][q / 2], q % 2 ? 0x0c030c02u : 0x0c010c00u);
+          if (chunk_cut(x, y)) {
+#pragma unroll
+            for (int j = 0; j < EC; ++j)
+              if (corner_cut(x + j, y)) kv[(b * EC + j) / 2] |= kTopKey << (j % 2 * 16);
           }
+#pragma unroll
+          for (int j = 0; j < EC; ++j)
+            if (live && x + j < a.bw) count(kv[(b * EC + j) / 2] >> (j % 2 * 16));
+        });
+      }
+      __syncthreads();
+      scan_counters();
+      __syncthreads();
+      chunks([&](int b, int x, int, bool live) {
+        uint32_t slot[EC] = {};
+#pragma unroll
+        for (int j = 0; j < EC; ++j)
+          if (live && x + j < a.bw) slot[j] = claim(kv[(b * EC + j) / 2] >> (j % 2 * 16));
+#pragma unroll
+        for (int j = 0; j < EC; j += 2) kv[(b * EC + j) / 2] = slot[j] | (slot[j + 1] << 16);
+      });
+      __syncthreads();
+      chunks([&](int b, int x, int y, bool live) {
+#pragma unroll
+        for (int j = 0; j < EC; ++j)
+          if (live && x + j < a.bw)
+            om_lds[(kv[(b * EC + j) / 2] >> (j % 2 * 16)) & 0xffffu] = (uint16_t)((y << 8) + x + j);
+      });
+      __syncthreads();
+      copy_om(om_lds);
+      __syncthreads();
+      // (the row pitch is even, and a pair may end in its padding)
+      chunks([&](int b, int x, int y, bool live) {
+        uint32_t* to = reinterpret_cast<uint32_t*>(I + y * a.pitch + x);
+#pragma unroll
+        for (int j = 0; j < EC; j += 2)
+          if (live && x + j < a.bw) to[j / 2] = kv[(b * EC + j) / 2];
+      });
+    } else if (a.off_sort) {
+      uint32_t kv[NB * EC];
+      {
+        u32x4 v[NB];
+        load_box(v);
+        clear_counters();
+        __syncthreads();
+        chunks([&](int b, int x, int y, bool live) {
+#pragma unroll
+          for (int j = 0; j < EC; ++j) kv[b * EC + j] = f32_to_key(v[b][j]);
+          if (chunk_cut(x, y)) {
+#pragma unroll
+            for (int j = 0; j < EC; ++j)
+              if (corner_cut(x + j, y)) kv[b * EC + j] = kTopKey;
+          }
+#pragma unroll
+          for (int j = 0; j < EC; ++j)
+            if (live && x + j < a.bw) count(kv[b * EC + j]);
+        });
+      }
+      __syncthreads();
+      scan_counters();
+      __syncthreads();
+      chunks([&](int b, int x, int, bool live) {
+        uint32_t slot[EC] = {};
+#pragma unroll
+        for (int j = 0; j < EC; ++j)
+          if (live && x + j < a.bw) slot[j] = claim(kv[b * EC + j]);
+#pragma unroll
+        for (int j = 0; j < EC; ++j) kv[b * EC + j] = (kv[b * EC + j] & 0xffff0000u) | slot[j];
+      });
+      __syncthreads();
+      uint32_t* words = reinterpret_cast<uint32_t*>(smem);
+      chunks([&](int b, int x, int y, bool live) {
+#pragma unroll
+        for (int j = 0; j < EC; ++j) {
+          const uint32_t k = kv[b * EC + j];
+          if (live && x + j < a.bw)
+            words[k & 0xffffu] = (k & 0xffff0000u) | (uint32_t)((y << 8) + x + j);
+        }
+      });
+      __syncthreads();
+      // the last pass writes the omnigram behind the ordinal image
+      uint16_t* om2 = reinterpret_cast<uint16_t*>(smem + a.off_hist);
+      lds_radix_sort<NB * EC>(words, T, reinterpret_cast<uint16_t*>(smem + a.off_sort), wsum,
+                              [&](uint32_t w, uint32_t o) {
+                                om2[o] = (uint16_t)w;
+                                I[(int)((w >> 8) & 255u) * a.pitch + (int)(w & 255u)] = (uint16_t)o;
+                              });
+      copy_om(om2);
+    } else {
+      // element e = e0 + j * kThreads + t, kGB per thread at a time
+      uint32_t* x0 = reinterpret_cast<uint32_t*>(gslot);
+      uint32_t* x1 = reinterpret_cast<uint32_t*>(gslot + a.off_x1);
+      constexpr int kGB = 8;
+      const int sx = kThreads % a.bw, sy = kThreads / a.bw;
+      auto load_batch = [&](int& lx, int& ly, uint32_t (&kk)[kGB], uint32_t (&ll)[kGB]) {
+#pragma unroll
+        for (int j = 0; j < kGB; ++j) {
+          // unconditional (remap keeps coordinates inside the image);
+          // elements numbered >= T are not used
+          const int gx = remap(gx0 + lx, a.w, a.boundary);
+          const int gy = remap(gy0 + ly, a.h, a.boundary);
+          ll[j] = (uint32_t)((ly << 8) | lx);
+          kk[j] = f32_to_key(static_cast<const uint32_t*>(a.img)[(long long)gy * a.stride + gx]);
+          if (corner_cut(lx, ly)) kk[j] = kTopKey;
+          lx += sx;
+          ly += sy;
+          if (lx >= a.bw) {
+            lx -= a.bw;
+            ly += 1;
+          }
+        }
+      };
+      clear_counters();
+      __syncthreads();
+      {
+        int lx = t % a.bw, ly = t / a.bw;
+        for (int e0 = 0; e0 < T; e0 += kGB * kThreads) {
+          uint32_t kk[kGB], ll[kGB];
+          load_batch(lx, ly, kk, ll);
+#pragma unroll
+          for (int j = 0; j < kGB; ++j)
+            if (e0 + j * kThreads + t < T) count(kk[j]);
+        }
+      }
+      __syncthreads();
+      scan_counters();
+      __syncthreads();
+      {
+        int lx = t % a.bw, ly = t / a.bw;
+        for (int e0 = 0; e0 < T; e0 += kGB * kThreads) {
+          uint32_t kk[kGB], ll[kGB], slot[kGB];
+          load_batch(lx, ly, kk, ll);
+#pragma unroll
+          for (int j = 0; j < kGB; ++j)
+            if (e0 + j * kThreads + t < T) slot[j] = claim(kk[j]);
+#pragma unroll
+          for (int j = 0; j < kGB; ++j)
+            if (e0 + j * kThreads + t < T) x0[slot[j]] = (kk[j] & 0xffff0000u) | ll[j];
+        }
+      }
+      __syncthreads();
+      global_radix_sort(x0, x1, T, 16, 2, om, pcnt, wsum);
+      // ordinal image (overwrites the count table): the omnigram is read kGI
+      // entries per thread at a time, loads in flight together
+      constexpr int kGI = 8;
+      for (int v0 = 0; v0 < T; v0 += kGI * kThreads) {
+        uint32_t loc[kGI];
+#pragma unroll
+        for (int j = 0; j < kGI; ++j) {
+          const int v = v0 + j * kThreads + t;
+          loc[j] = v < T ? (uint32_t)om[v] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kGI; ++j) {
+          const int v = v0 + j * kThreads + t;
+          if (v < T) I[(int)(loc[j] >> 8) * a.pitch + (int)(loc[j] & 255u)] = (uint16_t)v;
+        }
       }
     }
-    __syncthreads();
-    packed_exclusive_scan(pcnt, NW, wsum);
-    __syncthreads();
-    {
-      int lx = t % a.bw, ly = t / a.bw;
-      for (int e0 = 0; e0 < T; e0 += kGB * kThreads) {
-        uint32_t kk[kGB], ll[kGB], slot[kGB];
-        load_batch(e0, lx, ly, kk, ll);
-#pragma unroll
-        for (int j = 0; j < kGB; ++j)
-          if (e0 + j * kThreads + t < T) {
-            const uint32_t d = kk[j] & ((1u << KB) - 1u);
-            const uint32_t sh = (d & 1u) << 4;
-            slot[j] = (atomicAdd(&pcnt[d >> 1], 1u << sh) >> sh) & 0xffffu;
-          }
-#pragma unroll
-        for (int j = 0; j < kGB; ++j)
-          if (e0 + j * kThreads + t < T) {
-            if (KT == KEY_F32) x0[slot[j]] = (kk[j] & 0xffff0000u) | ll[j];
-            else om[slot[j]] = (uint16_t)ll[j];
-          }
-      }
-    }
-    __syncthreads();
-    if (KT == KEY_F32) global_radix_sort(x0, x1, T, 16, 2, om, pcnt, wsum);
   }
   if (a.counters && t == 0) atomicAdd(&a.counters[CNT_SORTED], (unsigned long long)(Tv - mlo));
-  // omnigram padding: locations outside the box (box width < 256)
+  // omnigram padding: locations outside the box (box width < 256); the copy
+  // of a global-scratch omnigram ends inside the padding, in this thread's
+  // order or another's, so it is fenced off
+  if constexpr (GS) __syncthreads();
   if (t < 16) om[Tv + t] = 0xffff;
   if (BR && t == 16) om[0] = 0xffff;
-  // 3. ordinal image (overwrites the sort's count table); a global-scratch
-  // omnigram is read kGI entries per thread at a time, loads in flight
-  // together
-  if constexpr (GS) {
-    constexpr int kGI = 8;
-    for (int v0 = mlo; v0 < Tv; v0 += kGI * kThreads) {
-      uint32_t loc[kGI];
-#pragma unroll
-      for (int j = 0; j < kGI; ++j) {
-        const int v = v0 + j * kThreads + t;
-        loc[j] = v < Tv ? (uint32_t)om[v] : 0u;
-      }
-#pragma unroll
-      for (int j = 0; j < kGI; ++j) {
-        const int v = v0 + j * kThreads + t;
-        if (v < Tv) I[(int)(loc[j] >> 8) * a.pitch + (int)(loc[j] & 255u)] = (uint16_t)v;
-      }
-    }
-  } else {
+  // 3. ordinal image (overwrites the sort's count table; global scratch:
+  // written above)
+  if constexpr (!GS)
     for (int v = mlo + t; v < Tv; v += kThreads) {
       const uint32_t loc = (uint32_t)om[v];
       I[(int)(loc >> 8) * a.pitch + (int)(loc & 255u)] = (uint16_t)v;
     }
-  }
   if (BR) {
     // pixels outside the bracket: bit c of the masks is box pixel
     // c * kThreads + t (coordinates stepped per chunk, as in the load)
