@@ -103,24 +103,26 @@ def box_union_px(lo, hi, dy_min, tw, th):
 
 
 def band_geometry(plan, w, h):
-    """Output pixels, histogram seeds, 16-column seed moves and horizontally
+    """Output pixels, histogram seeds, 8-column seed moves and horizontally
     slid pixels of one plain-filter launch, from the plan: bands of
-    ceil(th / (16 * 64 / tw)) rows, each band's first row cut into 16-column
-    chunks (the first from a histogram, the others moved from the previous
-    chunk's seed window), the rest of each chunk slid horizontally."""
+    2 * ceil(th / (16 * 64 / tw)) rows, each band's middle row cut into
+    8-column chunks shared by two waves (each wave's first chunk from a
+    histogram, the others moved from its previous chunk's seed window), the
+    rest of each chunk slid horizontally."""
     tw, th = plan["tile_w"], plan["tile_h"]
     segs = 64 // tw
-    R = -(-th // (16 * segs))
+    R = 2 * -(-th // (16 * segs))
     npx = seeds = moves = hslid = 0
     for ty0 in range(0, h, th):
         rows_in = min(th, h - ty0)
         bands = -(-rows_in // R)
         for tx0 in range(0, w, tw):
             cols_in = min(tw, w - tx0)
-            chunks = -(-cols_in // 16)
+            chunks = -(-cols_in // 8)
+            first = min(2, chunks)
             npx += rows_in * cols_in
-            seeds += bands
-            moves += bands * (chunks - 1)
+            seeds += bands * first
+            moves += bands * (chunks - first)
             hslid += bands * (cols_in - chunks)
     first_row = seeds + moves + hslid
     return dict(px=npx, seeds=seeds, moves=moves, hslid=hslid, vslid=npx - first_row)
@@ -133,7 +135,7 @@ def work_model(plan, fp, w, h, key_bits, blocks, groups):
              windows (T_union box pixels per tile) with P = key_bits / 8 byte
              passes of about 3 operations per element;
       slides 2 * cols compares per vertically slid pixel, 2 * rows per
-             horizontally slid pixel (a 16-column seed move counts as 16
+             horizontally slid pixel (an 8-column seed move counts as 8
              horizontal slides);
       scans  64 omnigram tests per wave-cooperative block, 8 per lane group
              (both counted by the kernel);
@@ -147,7 +149,7 @@ def work_model(plan, fp, w, h, key_bits, blocks, groups):
     passes = key_bits // 8
     g = band_geometry(plan, w, h)
     sort_ops = tiles * t_union * passes * 3
-    slide_ops = g["vslid"] * 2 * cols + (g["hslid"] + 16 * g["moves"]) * 2 * rows
+    slide_ops = g["vslid"] * 2 * cols + (g["hslid"] + 8 * g["moves"]) * 2 * rows
     scan_ops = 64 * blocks + 8 * groups
     seed_ops = g["seeds"] * fp.taps
     total = sort_ops + slide_ops + scan_ops + seed_ops

@@ -146,8 +146,8 @@ struct DeviceInfo {
 };
 int device_info(int dev, DeviceInfo* out);
 
-// Tile plans.  make_plan: everything in LDS; make_plan_gs: sort, omnigram and
-// reverse map in a global scratch slot.  choose_plan picks the tuned shape
+// Tile plans.  make_plan: everything in LDS; make_plan_gs: the omnigram in
+// a global scratch slot.  choose_plan picks the tuned shape
 // for this (dtype, footprint) if one is recorded, else the widest layout
 // that fits, LDS first; imax_cap bounds the register capacity of LDS plans.
 int make_plan(int dtype, const mf_footprint* fp, int lds_max, int tw, int th, ImageDesc* d);

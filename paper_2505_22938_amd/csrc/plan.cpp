@@ -185,10 +185,10 @@ int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
   const int ib = round_up(2 * d->pitch * d->bh, 16);
   const int hb = kHistBytes;
   const int B0 = std::max(kCounterBytes, ib + hb);
-  // slot: 8/16-bit keys: the omnigram (TP u16 entries), written by the
-  // counting pass.  Float keys: x0 and x1, TP 32-bit words each, for the
-  // stable passes over the high key bits; the last pass writes the omnigram
-  // over x0.  The output is read back from the image (no reverse map).
+  // slot: the omnigram (TP u16 entries).  Float keys: x0 and x1, TP 32-bit
+  // words each, for the stable passes over the high key bits where the words
+  // do not fit LDS; the last pass writes the omnigram over x0.  The output is
+  // read back from the image (no reverse map).
   // Region B also holds the sort's packed 16-bit key counters (2^16 of
   // them for 16-bit and float keys, 2^8 for 8-bit keys).
   int B = std::max(B0, dtype == MF_U8 ? 512 : 131072);

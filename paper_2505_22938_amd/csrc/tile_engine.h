@@ -855,9 +855,9 @@ __device__ __forceinline__ void chain_rerank(const D& a, int gx0, int gy0, uint3
 
 // One output tile.  All threads of the workgroup must call it.
 // GS = false: the sort, the omnigram and the reverse map live in LDS.
-// GS = true: they live in the workgroup's global scratch slot `gslot`
-// (boxes too large for LDS); the ordinal image, histograms and footprint
-// tables stay in LDS.
+// GS = true: the omnigram (and the words of float boxes too large to sort in
+// LDS) live in the workgroup's global scratch slot `gslot` (boxes too large
+// for LDS); the ordinal image, histograms and footprint tables stay in LDS.
 // BR = true (LDS variant only): the tile has a value bracket [lo, hi]
 // (a.brackets[tile], keys).  Only box pixels inside it are sorted; they take
 // ordinals 1..Tc, pixels below take ordinal 0 and pixels above 0xffff in the
@@ -1547,9 +1547,9 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   // the bracket.
   int m = 0, vp = 0, vc = k0, miss = 0;
 
-  // 4a. first rows of the wave's bands (paper, "GPU": seeds solved from
+  // 4a. first solved rows of the wave's bands (paper, "GPU": seeds solved from
   // histograms, then short horizontal slides from each seed).  The columns
-  // of each band's first row are cut into chunks of at most 16, each
+  // of each band's row are cut into chunks of at most CW, each
   // starting from its own seed window; the four 16-lane rows of the wave
   // take one chunk each and slide their windows right in lockstep: lane j
   // of a row counts the entering and leaving pixels of footprint rows j,
