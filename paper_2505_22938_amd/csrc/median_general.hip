@@ -129,34 +129,37 @@ int launch_window_pass(const void* img, int w, int h, size_t stride_bytes, int d
         return rc;
     return MF_OK;
   }
-  const void* table0 = nullptr;
-  if ((rc = footprint_device_table(outs[idx[0]].footprint, dev, &table0, stream))) return rc;
-  bind_image(&a, img, w, h, stride_bytes, dtype, &hull, boundary, 0, table0);
-  a.out = outs[idx[0]].out;
-  a.nq = n;
-  a.multi_fp = 1;
+  const void* tables[MF_MAX_RANK_OUTPUTS] = {};
   for (int q = 0; q < n; ++q) {
-    const mf_window_output& o = outs[idx[q]];
-    const mf_footprint* fp = o.footprint;
-    const void* table = nullptr;
-    if ((rc = footprint_device_table(fp, dev, &table, stream))) return rc;
-    PlaneFp& pf = a.pfp[q];
-    pf.spans = static_cast<const short2*>(table);
-    pf.dx_min = fp->dx_min;
-    pf.dy_min = fp->dy_min;
-    pf.nrows = (int)fp->row_lo.size();
-    pf.ncols = (int)fp->col_lo.size();
-    pf.limit = (int)fp->limit;
-    pf.rank_hi = fp->taps - 1;
-    if (pf.nrows > a.nrows || pf.ncols > a.ncols) return MF_ERR_UNSUPPORTED;   // not reached
-    a.outs[q] = o.out;
-    a.rmaps[q] = o.rank_map;
-    a.rmap_strides[q] = (long long)(o.rank_map_stride_bytes / 4);
-    a.ranks[q] = o.rank_map || o.rank < 0 ? (fp->taps - 1) / 2 : o.rank;
+    const mf_footprint* fp = outs[idx[q]].footprint;
+    if ((rc = footprint_device_table(fp, dev, &tables[q], stream))) return rc;
+    if ((int)fp->row_lo.size() > a.nrows || (int)fp->col_lo.size() > a.ncols)
+      return MF_ERR_UNSUPPORTED;   // not reached
   }
-  a.rank = a.ranks[0];
-  a.rank_hi = a.pfp[0].rank_hi;
-  return launch_with_plan(a, dev, di, stream);
+  return launch_fitted(a, dtype, &hull, w, h, dev, di, stream, [&](ImageDesc* d) {
+    bind_image(d, img, w, h, stride_bytes, dtype, &hull, boundary, 0, tables[0]);
+    d->out = outs[idx[0]].out;
+    d->nq = n;
+    d->multi_fp = 1;
+    for (int q = 0; q < n; ++q) {
+      const mf_window_output& o = outs[idx[q]];
+      const mf_footprint* fp = o.footprint;
+      PlaneFp& pf = d->pfp[q];
+      pf.spans = static_cast<const short2*>(tables[q]);
+      pf.dx_min = fp->dx_min;
+      pf.dy_min = fp->dy_min;
+      pf.nrows = (int)fp->row_lo.size();
+      pf.ncols = (int)fp->col_lo.size();
+      pf.limit = (int)fp->limit;
+      pf.rank_hi = fp->taps - 1;
+      d->outs[q] = o.out;
+      d->rmaps[q] = o.rank_map;
+      d->rmap_strides[q] = (long long)(o.rank_map_stride_bytes / 4);
+      d->ranks[q] = o.rank_map || o.rank < 0 ? (fp->taps - 1) / 2 : o.rank;
+    }
+    d->rank = d->ranks[0];
+    d->rank_hi = d->pfp[0].rank_hi;
+  });
 }
 
 PlainKernelFn pick_general_kernel(const ImageDesc& d) {
@@ -221,17 +224,18 @@ int median_filter_ranks(const void* img, int w, int h, size_t stride_bytes, int 
     return MF_OK;
   }
   if ((rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus))) return rc;
-  bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, (fp->taps - 1) / 2, table);
-  a.out = outs[0].out;
-  a.nq = nouts;
-  a.rank_hi = fp->taps - 1;
-  for (int q = 0; q < nouts; ++q) {
-    a.outs[q] = outs[q].out;
-    a.rmaps[q] = outs[q].rank_map;
-    a.rmap_strides[q] = (long long)(outs[q].rank_map_stride_bytes / 4);
-    a.ranks[q] = outs[q].rank_map ? (fp->taps - 1) / 2 : outs[q].rank;
-  }
-  return launch_with_plan(a, dev, di, stream);
+  return launch_fitted(a, dtype, fp, w, h, dev, di, stream, [&](ImageDesc* d) {
+    bind_image(d, img, w, h, stride_bytes, dtype, fp, boundary, (fp->taps - 1) / 2, table);
+    d->out = outs[0].out;
+    d->nq = nouts;
+    d->rank_hi = fp->taps - 1;
+    for (int q = 0; q < nouts; ++q) {
+      d->outs[q] = outs[q].out;
+      d->rmaps[q] = outs[q].rank_map;
+      d->rmap_strides[q] = (long long)(outs[q].rank_map_stride_bytes / 4);
+      d->ranks[q] = outs[q].rank_map ? (fp->taps - 1) / 2 : outs[q].rank;
+    }
+  });
 }
 
 int median_filter_windows(const void* img, int w, int h, size_t stride_bytes, int dtype,

@@ -165,9 +165,13 @@ int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
   if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, &a) != MF_OK &&
       (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
     return rc;
-  bind_image(&a, img, w, h, stride_bytes, dtype, fp, boundary, rank, table);
-  a.out = out;
-  return a.bits ? launch_bits(a, stream) : launch_with_plan(a, dev, di, stream);
+  auto bind = [&](ImageDesc* d) {
+    bind_image(d, img, w, h, stride_bytes, dtype, fp, boundary, rank, table);
+    d->out = out;
+  };
+  bind(&a);
+  return a.bits ? launch_bits(a, stream)
+                : launch_fitted(a, dtype, fp, w, h, dev, di, stream, bind);
 }
 
 // Chained tiles (median_filter_chained): the plan of the footprint with an

@@ -207,6 +207,25 @@ using PlainKernelFn = void (*)(ImageDesc);
 int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t stream,
                      unsigned char* ext_scratch = nullptr, size_t ext_bytes = 0);
 PlainKernelFn pick_general_kernel(const ImageDesc& d);
+// The same for the plan of choose_plan(.., spread): where that is a
+// global-scratch plan and the scratch is not to be had (a capturing stream
+// without cached scratch, no memory), the default plan `bind` fills in
+// again, if it needs none.
+template <typename Bind>
+int launch_fitted(ImageDesc a, int dtype, const mf_footprint* fp, int w, int h, int dev,
+                  const DeviceInfo& di, hipStream_t stream, Bind&& bind) {
+  bind(&a);
+  int rc = launch_with_plan(a, dev, di, stream);
+  if (a.gs && (rc == MF_ERR_UNSUPPORTED || rc == MF_ERR_NOMEM)) {
+    ImageDesc b{};
+    (void)hipGetLastError();
+    if (choose_plan(dtype, fp, di.lds_max, 33, &b, w, h, di.cus, false) == MF_OK && !b.gs) {
+      bind(&b);
+      rc = launch_with_plan(b, dev, di, stream);
+    }
+  }
+  return rc;
+}
 // Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
 // kernel, and launch with a complete plan.
 // us (optional): the estimated time of the image.
