@@ -140,6 +140,18 @@ struct ImageDesc {
   int off_fwd;
 };
 
+// Vertical slide of a window by one row over the ordinal image: the entering
+// pixel (low half) and the leaving one (high half) of window column j, whose
+// pixels are rows lo .. hi of the window's offset rectangle, as 16-bit
+// elements from the rectangle's top left before the slide (going up: from one
+// row above that).  Either way the two lie on rows lo and hi + 1 from there,
+// so the largest is nrows * pitch + ncols - 1, and the plan's pitch keeps that
+// below 2^16.
+__host__ __device__ inline uint32_t slide_offsets(int lo, int hi, int pitch, int j, bool up) {
+  const uint32_t top = (uint32_t)(lo * pitch + j), below = (uint32_t)((hi + 1) * pitch + j);
+  return up ? top | (below << 16) : below | (top << 16);
+}
+
 struct DeviceInfo {
   int lds_max = 0;
   int cus = 0;

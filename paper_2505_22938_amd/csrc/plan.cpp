@@ -40,9 +40,12 @@ int band_geometry(const mf_footprint* fp, int tw, int th, ImageDesc* d) {
   const int T = bw * bh;
   if (T > 65535) return MF_ERR_UNSUPPORTED;
   // ordinal-image row pitch (16-bit elements): pitch/2 odd, so consecutive
-  // rows start in different LDS banks
+  // rows start in different LDS banks, unless that takes an offset of the
+  // vertical slides past 16 bits (boxes 255 wide under windows of 254 rows and
+  // more, tiles of at most three rows; one row does not slide)
   int pitch = round_up(bw, 2);
-  if ((pitch / 2) % 2 == 0) pitch += 2;
+  const int nrows = fp->dy_max - fp->dy_min + 1, ncols = fp->dx_max - fp->dx_min + 1;
+  if ((pitch / 2) % 2 == 0 && nrows * (pitch + 2) + ncols - 1 <= 65535) pitch += 2;
   d->tw = tw;
   d->th = th;
   d->bw = bw;

@@ -924,11 +924,10 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
   int mlo = 0;       // smallest ordinal a member may have
 
   // footprint tables: row spans, per-row horizontal offsets relative to the
-  // window centre, per-column vertical offsets (entering | leaving << 16)
-  // relative to the box position one row above and at the left end of the
-  // window's offset rectangle: one table for slides down, one for slides up,
-  // each padded to a multiple of eight columns whose two offsets cancel
-  // (windows of fewer than four columns: not padded).  Planes with windows of
+  // window centre, per-column vertical offsets (slide_offsets): one table for
+  // slides down, one for slides up, each padded to a multiple of eight columns
+  // whose two offsets cancel (windows of fewer than four columns: not padded).
+  // Planes with windows of
   // their own (multi_fp) rebuild them per plane inside the box of the plan,
   // whose offsets (a.dx_min, a.dy_min) still place the centres.
   auto vcols8 = [](int ncols) { return ncols >= 4 ? (ncols + 7) & ~7 : 0; };
@@ -942,12 +941,8 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
     const int n8 = vcols8(ncols), n = n8 ? n8 : ncols;
     for (int j = t; j < n; j += kThreads) {
       const short2 s = j < ncols ? spans[nrows + j] : make_short2(0, 0);
-      // rows from one above the rectangle's top
-      const uint32_t r0 = (uint32_t)((s.x - dy_min + 1) * a.pitch + j);
-      const uint32_t r1 = (uint32_t)((s.y - dy_min + 1) * a.pitch + j);
-      const uint32_t P = (uint32_t)a.pitch;
-      vtab[j] = j < ncols ? (r1 + P) | (r0 << 16) : 0u;
-      vtab[n + j] = j < ncols ? (r0 - P) | (r1 << 16) : 0u;
+      vtab[j] = j < ncols ? slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, j, false) : 0u;
+      vtab[n + j] = j < ncols ? slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, j, true) : 0u;
     }
   };
   const bool mfp = GEN && a.multi_fp;
@@ -1735,9 +1730,9 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
     const int gx = tx0 + col, gy = ty0 + row;
     const int kl = rank_at<GEN>(a, q, k0, gx, gy, lane_active);
     const int cy_prev = row - dir - a.dy_min;
-    // LDS address of the previous window's rectangle, one row above it
-    const uint32_t lb = lds_address(I) +
-                        (uint32_t)(2 * ((cy_prev + f.dy_min - 1) * a.pitch + cxl + fdx_min));
+    // LDS address of the previous window's rectangle (going up: one row above)
+    const uint32_t lb = lds_address(I) + (uint32_t)(2 * ((cy_prev + f.dy_min - (up ? 1 : 0)) * a.pitch +
+                                                         cxl + fdx_min));
     const int delta = lane_active ? slide_count(vt, n8, fcols, lb, vp) : 0;
     int pl = vp, cl = vc + delta;
     int mnew = m, esc = 0;
