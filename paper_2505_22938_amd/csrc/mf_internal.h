@@ -151,6 +151,10 @@ __host__ __device__ inline uint32_t slide_offsets(int lo, int hi, int pitch, int
   const uint32_t top = (uint32_t)(lo * pitch + j), below = (uint32_t)((hi + 1) * pitch + j);
   return up ? top | (below << 16) : below | (top << 16);
 }
+// A column that counts nothing: the leaving pixel of `o` twice, a pixel of the
+// window before the slide and so in the box (the place the offsets count from
+// may lie above it: chained tiles slide from the row above the tile).
+__host__ __device__ inline uint32_t slide_padding(uint32_t o) { return (o & 0xffff0000u) | (o >> 16); }
 
 struct DeviceInfo {
   int lds_max = 0;

@@ -940,9 +940,12 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
     }
     const int n8 = vcols8(ncols), n = n8 ? n8 : ncols;
     for (int j = t; j < n; j += kThreads) {
-      const short2 s = j < ncols ? spans[nrows + j] : make_short2(0, 0);
-      vtab[j] = j < ncols ? slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, j, false) : 0u;
-      vtab[n + j] = j < ncols ? slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, j, true) : 0u;
+      const int c = j < ncols ? j : 0;
+      const short2 s = spans[nrows + c];
+      const uint32_t dn = slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, c, false);
+      const uint32_t up = slide_offsets(s.x - dy_min, s.y - dy_min, a.pitch, c, true);
+      vtab[j] = j < ncols ? dn : slide_padding(dn);
+      vtab[n + j] = j < ncols ? up : slide_padding(up);
     }
   };
   const bool mfp = GEN && a.multi_fp;

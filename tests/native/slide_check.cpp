@@ -2,6 +2,8 @@
 // many windows and of low tiles (whose boxes are the tallest), the two 16-bit
 // offsets of each column hold the exact positions of the entering and leaving
 // pixels, and those lie in the ordinal image whatever row the slide goes to.
+// So do the padding columns' two, in chained tiles too, which slide from the
+// row above the tile.
 #include <cstdio>
 #include <vector>
 
@@ -39,6 +41,25 @@ void check(const mf::ImageDesc& d, const mf_footprint* fp) {
   }
 }
 
+// Padding columns of d's tables, for slides that start from tile rows r0 on.
+void check_padding(const mf::ImageDesc& d, const mf_footprint* fp, int r0) {
+  ++checked;
+  const int lo = fp->col_lo[0] - fp->dy_min, hi = fp->col_hi[0] - fp->dy_min;
+  for (const bool up : {false, true}) {
+    if (up && r0 < 0) continue;   // (chained tiles slide down only)
+    const uint32_t o = mf::slide_padding(mf::slide_offsets(lo, hi, d.pitch, 0, up));
+    bool ok = (o & 0xffffu) == o >> 16;
+    for (const int row : {up ? 1 : r0, up ? d.th - 1 : d.th - 2})
+      for (const int col : {0, d.tw - 1}) {
+        const int at = (row - (up ? 1 : 0)) * d.pitch + col + (int)(o >> 16);
+        ok = ok && at >= 0 && at < d.pitch * d.bh;
+      }
+    if (!ok && failures++ < 20)
+      std::printf("padding: tile %dx%d box %dx%d window %zux%zu up %d from row %d: %u\n", d.tw, d.th,
+                  d.bw, d.bh, fp->row_lo.size(), fp->col_lo.size(), up, r0, o);
+  }
+}
+
 void walk(const mf_footprint* fp) {
   const int lds_max = 160 * 1024;
   for (int dtype : {MF_U8, MF_U16, MF_F32})
@@ -46,7 +67,12 @@ void walk(const mf_footprint* fp) {
       for (int th : {2, 3, 4, 5, 6, 7, 8, 11, 16, 48, 128}) {   // (one row does not slide)
         mf::ImageDesc d{};
         if (mf::make_plan(dtype, fp, lds_max, tw, th, &d) == MF_OK) check(d, fp);
-        if (mf::make_plan_gs(dtype, fp, lds_max, tw, th, &d) == MF_OK) check(d, fp);
+        if (mf::make_plan_gs(dtype, fp, lds_max, tw, th, &d) == MF_OK) {
+          check(d, fp);
+          check_padding(d, fp, 0);
+        }
+        const mf_footprint* fx = mf::footprint_with_top_row(fp);
+        if (mf::make_plan(dtype, fx, lds_max - 128, tw, th, &d) == MF_OK) check_padding(d, fx, -1);
       }
 }
 
