@@ -75,6 +75,10 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   if (tw > 0 || work_counters_ptr()) return MF_ERR_UNSUPPORTED;
   const int H = (int)fp->row_lo.size(), W = (int)fp->col_lo.size(), es = elem_size(dtype);
   if (H > 64) return MF_ERR_UNSUPPORTED;   // the tap table is built by one wave, a row per lane
+  // the filter's limit on windows is the tile engine's, whichever path runs:
+  // the window's width and height in the smallest tile's box
+  ImageDesc smallest{};
+  if (make_plan_gs(dtype, fp, lds_max, 8, 8, &smallest) != MF_OK) return MF_ERR_UNSUPPORTED;
   int pairs = 0;
   for (int i = 0; i < H; ++i) {
     if (fp->row_hi[i] < fp->row_lo[i]) return MF_ERR_UNSUPPORTED;
