@@ -135,7 +135,10 @@ void mf_footprint_destroy(mf_footprint* fp);
  * captured needs one uncaptured call with the same footprint, dtype and an
  * image at least as large on that stream first.  Scratch used by a captured
  * call stays allocated (and is not reused for a larger size) until
- * mf_release_scratch.
+ * mf_release_scratch.  Graphs that use the scratch of one stream, and eager
+ * calls on it, must not overlap in time.  Windows whose boxes sort in LDS
+ * (mf_query_plan's shape: disc radii to 48 or so) put no scratch into a graph,
+ * though eager calls may take scratch for them.
  * ------------------------------------------------------------------------ */
 int median_filter(const void* img, int w, int h, size_t stride_bytes, int dtype,
                   const mf_footprint* fp, int boundary, void* out, hipStream_t stream);

@@ -120,7 +120,7 @@ unsigned long long* work_counters_ptr() { return g_counters; }
 // Launch one plain filter with a complete plan `a` (geometry + image bound);
 // a.nq > 0 selects the general-rank kernels.
 int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t stream,
-                     unsigned char* ext_scratch, size_t ext_bytes) {
+                     unsigned char* ext_scratch, size_t ext_bytes, size_t keep_bytes) {
   a.counters = g_counters;
   KernelFn k = a.nq > 0 ? pick_general_kernel(a) : pick_kernel(a);
   (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -129,8 +129,7 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
   if (ntiles > 0x7fffffffLL) return MF_ERR_UNSUPPORTED;
   long long grid = ntiles;
   if (a.gs) {
-    const int occ = std::max(1, std::min(2, di.lds_max / std::max(1, a.lds_bytes)));
-    grid = std::min<long long>(ntiles, (long long)di.cus * occ);
+    grid = scratch_slots(a, di);
     if (ext_scratch) {
       // claim words first (zero-initialised, left zero by every launch)
       if (ext_bytes < (size_t)kClaimBytes) return MF_ERR_SCRATCH_LIMIT;
@@ -140,7 +139,7 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
       a.scratch = ext_scratch + kClaimBytes;
     } else {
       void* scr = nullptr;
-      const int rc = get_scratch(dev, stream, (size_t)grid * (size_t)a.slot_bytes, &scr);
+      const int rc = get_scratch(dev, stream, (size_t)grid * (size_t)a.slot_bytes, &scr, keep_bytes);
       if (rc) return rc;
       a.scratch = static_cast<unsigned char*>(scr);
     }

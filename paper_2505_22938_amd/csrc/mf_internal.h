@@ -197,9 +197,10 @@ int validate_image(const void* img, int w, int h, size_t stride_bytes, int dtype
 // every cached buffer (mf_release_scratch).  *out points to `bytes` of slot
 // space; the kClaimBytes before it hold the tile-claim words (nine used),
 // zeroed when the buffer is allocated and left zero by every launch that
-// uses them.
+// uses them.  Outside capture the buffer is grown to keep_bytes if that is more
+// and there is memory for it.
 constexpr int kClaimBytes = 256;
-int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out);
+int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out, size_t keep_bytes = 0);
 int release_scratch();
 
 // Tuned tile shapes, keyed by dtype and footprint.
@@ -218,29 +219,50 @@ unsigned long long* work_counters_ptr();
 // ext_scratch (non-null): a global-scratch plan takes its slots from this
 // buffer of ext_bytes bytes instead of the cached per-stream scratch, its
 // persistent grid shrunk to the slots that fit (MF_ERR_SCRATCH_LIMIT if not
-// even one does); nothing is allocated.
+// even one does); nothing is allocated.  keep_bytes: cached scratch that is
+// allocated holds at least that much where there is memory for it.
 using PlainKernelFn = void (*)(ImageDesc);
 int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t stream,
-                     unsigned char* ext_scratch = nullptr, size_t ext_bytes = 0);
+                     unsigned char* ext_scratch = nullptr, size_t ext_bytes = 0,
+                     size_t keep_bytes = 0);
 PlainKernelFn pick_general_kernel(const ImageDesc& d);
-// The same for the plan of choose_plan(.., spread): where that is a
-// global-scratch plan and the scratch is not to be had (a capturing stream
-// without cached scratch, no memory), the default plan `bind` fills in
-// again, if it needs none.
+// Workgroups of a global-scratch plan bound to its image, a slot each.
+long long scratch_slots(const ImageDesc& a, const DeviceInfo& di);
+// The LDS shape of least estimated time (MF_ERR_UNSUPPORTED: no box fits).
+int lds_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h, int cus,
+             ImageDesc* d);
+// The same for the plan of choose_plan(.., spread), completed by `bind`.  Scratch
+// belongs to the stream: graphs captured on one stream bake in the same buffer
+// and tile claims, and hipStreamPerThread names a stream of each thread.  So a
+// window whose default plan is an LDS one runs on that there, and the fitted
+// global-scratch plan is for calls that the stream orders.  Where scratch is not
+// to be had (a capturing stream with too little, no memory) the default plan and
+// then an LDS one are tried.  An uncaptured call leaves the stream the scratch of
+// its default plan too, which is what a captured call on a smaller image takes.
 template <typename Bind>
 int launch_fitted(ImageDesc a, int dtype, const mf_footprint* fp, int w, int h, int dev,
                   const DeviceInfo& di, hipStream_t stream, Bind&& bind) {
   bind(&a);
-  int rc = launch_with_plan(a, dev, di, stream);
-  if (a.gs && (rc == MF_ERR_UNSUPPORTED || rc == MF_ERR_NOMEM)) {
-    ImageDesc b{};
-    (void)hipGetLastError();
-    if (choose_plan(dtype, fp, di.lds_max, 33, &b, w, h, di.cus, false) == MF_OK && !b.gs) {
-      bind(&b);
-      rc = launch_with_plan(b, dev, di, stream);
-    }
-  }
-  return rc;
+  if (!a.gs) return launch_with_plan(a, dev, di, stream);
+  ImageDesc d{};
+  int rc = choose_plan(dtype, fp, di.lds_max, 33, &d, w, h, di.cus, false);
+  if (rc) return rc;
+  bind(&d);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) return MF_ERR_HIP;
+  if (!d.gs && (cap != hipStreamCaptureStatusNone || stream == hipStreamPerThread))
+    return launch_with_plan(d, dev, di, stream);
+  rc = launch_with_plan(a, dev, di, stream, nullptr, 0,
+                        d.gs ? (size_t)scratch_slots(d, di) * (size_t)d.slot_bytes : 0);
+  if (rc != MF_ERR_UNSUPPORTED && rc != MF_ERR_NOMEM) return rc;
+  (void)hipGetLastError();
+  rc = launch_with_plan(d, dev, di, stream);
+  if (rc != MF_ERR_UNSUPPORTED && rc != MF_ERR_NOMEM) return rc;
+  (void)hipGetLastError();
+  ImageDesc l{};
+  if (lds_plan(dtype, fp, di.lds_max, 33, w, h, di.cus, &l) != MF_OK) return rc;
+  bind(&l);
+  return launch_with_plan(l, dev, di, stream);
 }
 // Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
 // kernel, and launch with a complete plan.

@@ -444,6 +444,22 @@ static void spread_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
     }
 }
 
+int lds_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h, int cus,
+             ImageDesc* d) {
+  double best = 1e300;
+  for (int tw : {64, 48, 32, 16, 8})
+    for (int th : {128, 112, 96, 80, 64, 48, 32, 16, 8}) {
+      ImageDesc c{};
+      if (make_plan(dtype, fp, lds_max, tw, th, &c) != MF_OK || c.imax > imax_cap) continue;
+      const double us = plan_us(c, w, h, cus);
+      if (us < best) {
+        best = us;
+        *d = c;
+      }
+    }
+  return best < 1e300 ? MF_OK : MF_ERR_UNSUPPORTED;
+}
+
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
                 int w, int h, int cus, bool spread) {
   int tw = 0, th = 0;
@@ -539,6 +555,7 @@ struct ScratchEntry {
   void* ptr;
   size_t bytes;
   bool captured;   // a graph captured on the stream may still use ptr
+  size_t asked;    // largest size an allocation was tried for
 };
 std::mutex g_scratch_mu;
 std::vector<ScratchEntry> g_scratch;
@@ -551,14 +568,26 @@ std::vector<std::pair<int, void*>> g_retired;   // outgrown but possibly capture
 // returns MF_ERR_UNSUPPORTED.  Outside capture a buffer that is too small is
 // replaced; if a captured graph may refer to the old one it is retired, not
 // freed.
-int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out) {
+int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out, size_t keep_bytes) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) return MF_ERR_HIP;
   const bool capturing = cap != hipStreamCaptureStatusNone;
+  size_t want = capturing ? bytes : std::max(bytes, keep_bytes);
+  const size_t asked = want;
+  auto grab = [&](void** p) {
+    if (hipMalloc(p, kClaimBytes + want) == hipSuccess) return true;
+    *p = nullptr;
+    if (want == bytes) return false;
+    (void)hipGetLastError();
+    want = bytes;
+    if (hipMalloc(p, kClaimBytes + want) == hipSuccess) return true;
+    *p = nullptr;
+    return false;
+  };
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   for (auto& e : g_scratch) {
     if (e.dev == dev && e.stream == stream) {
-      if (e.bytes < bytes) {
+      if (e.bytes < bytes || e.asked < want) {
         if (capturing) return MF_ERR_UNSUPPORTED;
         if (hipStreamSynchronize(stream) != hipSuccess) return MF_ERR_HIP;
         if (e.captured) g_retired.push_back({dev, e.ptr});
@@ -566,10 +595,11 @@ int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out) {
         e.ptr = nullptr;
         e.bytes = 0;
         e.captured = false;
-        if (hipMalloc(&e.ptr, kClaimBytes + bytes) != hipSuccess) return MF_ERR_NOMEM;
+        if (!grab(&e.ptr)) return MF_ERR_NOMEM;
         if (hipMemsetAsync(e.ptr, 0, kClaimBytes, stream) != hipSuccess) return MF_ERR_HIP;
-        e.bytes = bytes;
+        e.bytes = want;
       }
+      e.asked = std::max(e.asked, asked);
       e.captured = e.captured || capturing;
       *out = static_cast<unsigned char*>(e.ptr) + kClaimBytes;
       return MF_OK;
@@ -577,14 +607,19 @@ int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out) {
   }
   if (capturing) return MF_ERR_UNSUPPORTED;
   void* p = nullptr;
-  if (hipMalloc(&p, kClaimBytes + bytes) != hipSuccess) return MF_ERR_NOMEM;
+  if (!grab(&p)) return MF_ERR_NOMEM;
   if (hipMemsetAsync(p, 0, kClaimBytes, stream) != hipSuccess) {
     (void)hipFree(p);
     return MF_ERR_HIP;
   }
-  g_scratch.push_back({dev, stream, p, bytes, false});
+  g_scratch.push_back({dev, stream, p, want, false, asked});
   *out = static_cast<unsigned char*>(p) + kClaimBytes;
   return MF_OK;
+}
+
+long long scratch_slots(const ImageDesc& a, const DeviceInfo& di) {
+  const int occ = std::max(1, std::min(2, di.lds_max / std::max(1, a.lds_bytes)));
+  return std::min<long long>((long long)a.tiles_x * a.tiles_y, (long long)di.cus * occ);
 }
 
 int release_scratch() {
