@@ -521,7 +521,7 @@ def leg_configs(torch, mf, img, img_np, reps, check_oracle, log):
             torch, lambda: mf.median_filter(img, fp, "clamp", out=out), stream, reps)))
         r = {"image": f"{w}x{h} uint16 natural-like (the headline image)",
              "window": f"disc r={rad} ({fp.taps} taps)", "boundary": "clamp", "ms": ms,
-             "mpx_s": w * h / 1e3 / ms, "plan": mf.query_plan(w, h, mf.MF_U16, fp)}
+             "mpx_s": w * h / 1e3 / ms, "plan": mf.query_call(w, h, mf.MF_U16, fp)}
         if check_oracle:
             r["oracle_mismatches"] = _oracle_sample(img_np, OF.disc(rad), out.cpu().numpy(),
                                                     1000, 40 + rad)
@@ -586,6 +586,39 @@ def leg_stress(torch, mf, reps, check_oracle, log):
     return res
 
 
+def tile_roofline(torch, mf, img, out, fp, plan, S, full, kern_ms):
+    """Work of one plain call on the S x S image by the tile engine, against
+    the vector ALU; `full`: the headline workload, whose counter summaries are kept."""
+    # work counters (separate, untimed call)
+    mf.work_counters(1)
+    mf.median_filter(img, fp, "clamp", out=out)
+    torch.cuda.synchronize()
+    cnt = mf.work_counters(-1)
+    blocks, seeds, groups = cnt[0], cnt[1], cnt[6]
+    nw = max(cnt[5], 1)
+    phase_clk = {"sort": cnt[2] / nw, "rows": cnt[3] / nw, "sweep": cnt[4] / nw,
+                 "seeds": cnt[8] / nw, "load": cnt[9] / nw}
+    mf.work_counters(0)
+    wm = work_model(plan, fp, S, S, 16, blocks, groups)
+    if wm["seeds"] != seeds:
+        print(f"# note: kernel counted {seeds} histogram seeds, plan geometry {wm['seeds']}",
+              file=sys.stderr, flush=True)
+    kmean = float(np.mean(kern_ms))
+    achieved = wm["total"] / (kmean * 1e-3)
+    traffic = measured_traffic(plan) if full else None
+    issued = issued_lane_ops(plan) if full else None
+    return {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
+            "unit": "Top/s (int32 lane-ops)", "frac": achieved / VALU_PEAK_OPS,
+            "traffic": traffic, "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
+            "hbm_gb_s": traffic / (kmean * 1e-3) / 1e9 if traffic else None,
+            "hbm_frac_of_8tb_s": traffic / (kmean * 1e-3) / 8e12 if traffic else None,
+            "kernel_ms_mean": kmean, "kernel_ms_min": float(np.min(kern_ms)),
+            "algorithmic_lane_ops": wm["total"],
+            "issued_lane_ops": issued,
+            "issued_over_algorithmic": issued / wm["total"] if issued else None,
+            "work_lane_ops": wm, "clocks_per_wave": phase_clk}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -620,7 +653,7 @@ def main():
     img = torch.from_numpy(img_np).to(dev)
     out = torch.empty_like(img)
     fp = mf.Footprint.disc(r)
-    plan = mf.query_plan(S, S, mf.MF_U16, fp)
+    plan = mf.query_call(S, S, mf.MF_U16, fp)
     print(f"# input ready in {time.time() - t0:.1f}s; plan {plan}", file=sys.stderr, flush=True)
 
     stream = torch.cuda.current_stream()
@@ -643,35 +676,11 @@ def main():
     mpx = S * S / 1e6
     value = mpx * args.steps / wall
 
-    # work counters (separate, untimed call)
-    mf.work_counters(1)
-    mf.median_filter(img, fp, "clamp", out=out)
-    torch.cuda.synchronize()
-    cnt = mf.work_counters(-1)
-    blocks, seeds, groups = cnt[0], cnt[1], cnt[6]
-    nw = max(cnt[5], 1)
-    phase_clk = {"sort": cnt[2] / nw, "rows": cnt[3] / nw, "sweep": cnt[4] / nw,
-                 "seeds": cnt[8] / nw, "load": cnt[9] / nw}
-    mf.work_counters(0)
-    wm = work_model(plan, fp, S, S, 16, blocks, groups)
-    if wm["seeds"] != seeds:
-        print(f"# note: kernel counted {seeds} histogram seeds, plan geometry {wm['seeds']}",
-              file=sys.stderr, flush=True)
     kmean = float(np.mean(kern_ms))
-    achieved = wm["total"] / (kmean * 1e-3)
-    full = (S, r) == (4096, 32)
-    traffic = measured_traffic(plan) if full else None
-    issued = issued_lane_ops(plan) if full else None
-    roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
-                "unit": "Top/s (int32 lane-ops)", "frac": achieved / VALU_PEAK_OPS,
-                "traffic": traffic, "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-                "hbm_gb_s": traffic / (kmean * 1e-3) / 1e9 if traffic else None,
-                "hbm_frac_of_8tb_s": traffic / (kmean * 1e-3) / 8e12 if traffic else None,
-                "kernel_ms_mean": kmean, "kernel_ms_min": float(np.min(kern_ms)),
-                "algorithmic_lane_ops": wm["total"],
-                "issued_lane_ops": issued,
-                "issued_over_algorithmic": issued / wm["total"] if issued else None,
-                "work_lane_ops": wm, "clocks_per_wave": phase_clk}
+    roofline = {"kernel_ms_mean": kmean, "kernel_ms_min": float(np.min(kern_ms))}
+    # (the counters and the work model are the tile engine's)
+    if plan["path"] != "bits":
+        roofline = tile_roofline(torch, mf, img, out, fp, plan, S, (S, r) == (4096, 32), kern_ms)
     gpu_out = out.cpu().numpy()
 
     if args.copy_check:

@@ -425,6 +425,21 @@ int mf_tune_cache_save(const char* path);
 int mf_query_plan(int w, int h, int dtype, const mf_footprint* fp, int* tile_w, int* tile_h,
                   int* box_w, int* box_h, int* lds_bytes);
 
+/* What a median_filter call on such an image runs, outside graph capture and
+ * with memory to be had: the path, on bit planes the variant (its index; -1
+ * for tiles), the output tile, its input box, the LDS bytes per workgroup and
+ * the bytes of scratch it needs of its stream.  Overrides, the tuned table and
+ * enabled work counters count as in the call.  Any output pointer may be NULL.
+ * Host-only; runs no GPU code. */
+typedef enum {
+  MF_PATH_LDS = 0,     /* tiles whose boxes sort in LDS                     */
+  MF_PATH_SCRATCH = 1, /* tiles whose omnigram lies in global scratch       */
+  MF_PATH_BITS = 2     /* bit planes                                        */
+} mf_path;
+int mf_query_call(int w, int h, int dtype, const mf_footprint* fp, int* path, int* variant,
+                  int* tile_w, int* tile_h, int* box_w, int* box_h, int* lds_bytes,
+                  long long* scratch_bytes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -63,6 +63,7 @@ def lib():
         "mf_set_tile_override": ([I, I], I),
         "mf_release_scratch": ([], I),
         "mf_query_plan": ([I, I, I, P, IP, IP, IP, IP, IP], I),
+        "mf_query_call": ([I, I, I, P, IP, IP, IP, IP, IP, IP, IP, ctypes.POINTER(LL)], I),
         "mf_work_counters": ([I, P], I),
         "mf_autotune": ([P, I, I, SZ, I, P, I, P, P, I, IP, IP,
                          ctypes.POINTER(ctypes.c_float)], I),
@@ -449,6 +450,24 @@ def query_plan(w: int, h: int, dtype: int, fp: Footprint):
     _check("mf_query_plan", lib().mf_query_plan(w, h, dtype, fp.handle,
                                                 *[ctypes.byref(v) for v in vals]))
     return dict(zip(("tile_w", "tile_h", "box_w", "box_h", "lds_bytes"), (v.value for v in vals)))
+
+
+PATHS = ("lds", "scratch", "bits")
+
+
+def query_call(w: int, h: int, dtype: int, fp: Footprint):
+    """What a median_filter call on such an image runs: the path ("lds" or
+    "scratch" tiles, or "bits"), the bit-plane variant (-1: tiles), its tile,
+    box, LDS bytes and scratch bytes."""
+    vals = [ctypes.c_int() for _ in range(7)]
+    scratch = ctypes.c_longlong()
+    _check("mf_query_call", lib().mf_query_call(w, h, dtype, fp.handle,
+                                                *[ctypes.byref(v) for v in vals],
+                                                ctypes.byref(scratch)))
+    names = ("path", "variant", "tile_w", "tile_h", "box_w", "box_h", "lds_bytes")
+    res = dict(zip(names, (v.value for v in vals)), scratch_bytes=scratch.value)
+    res["path"] = PATHS[res["path"]]
+    return res
 
 
 class _ImageDesc(ctypes.Structure):

@@ -150,6 +150,13 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
   return MF_OK;
 }
 
+// The plan of a plain call: bit planes or tiles fitted to the image.
+static int call_plan(int dtype, const mf_footprint* fp, const DeviceInfo& di, int w, int h,
+                     ImageDesc* d) {
+  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, d) == MF_OK) return MF_OK;
+  return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus);
+}
+
 int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
                  const mf_footprint* fp, int boundary, int rank, void* out, hipStream_t stream) {
   int dev = 0;
@@ -161,9 +168,7 @@ int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
   rc = footprint_device_table(fp, dev, &table, stream);
   if (rc) return rc;
   ImageDesc a{};
-  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, &a) != MF_OK &&
-      (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
-    return rc;
+  if ((rc = call_plan(dtype, fp, di, w, h, &a))) return rc;
   auto bind = [&](ImageDesc* d) {
     bind_image(d, img, w, h, stride_bytes, dtype, fp, boundary, rank, table);
     d->out = out;
@@ -205,14 +210,30 @@ int launch_chained(const void* img, int w, int h, size_t stride_bytes, int dtype
   return MF_OK;
 }
 
-int query_plan(int w, int h, int dtype, const mf_footprint* fp, ImageDesc* d) {
+// The current device, or the target's numbers where there is none.
+static DeviceInfo query_device() {
   int dev = 0;
   DeviceInfo di;
   if (hipGetDevice(&dev) != hipSuccess || device_info(dev, &di) != MF_OK) {
     di.lds_max = 160 * 1024;
     di.cus = 256;
   }
+  return di;
+}
+
+int query_plan(int w, int h, int dtype, const mf_footprint* fp, ImageDesc* d) {
+  const DeviceInfo di = query_device();
   return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus, false);
+}
+
+int query_call(int w, int h, int dtype, const mf_footprint* fp, ImageDesc* d, long long* scratch) {
+  const DeviceInfo di = query_device();
+  const int rc = call_plan(dtype, fp, di, w, h, d);
+  if (rc) return rc;
+  d->tiles_x = (w + d->tw - 1) / d->tw;
+  d->tiles_y = (h + d->th - 1) / d->th;
+  *scratch = d->gs ? scratch_slots(*d, di) * d->slot_bytes : 0;
+  return MF_OK;
 }
 
 int set_counters(int enable) {
@@ -296,6 +317,26 @@ int mf_query_plan(int w, int h, int dtype, const mf_footprint* fp, int* tile_w, 
   if (box_w) *box_w = d.bw;
   if (box_h) *box_h = d.bh;
   if (lds) *lds = d.lds_bytes;
+  return MF_OK;
+}
+
+int mf_query_call(int w, int h, int dtype, const mf_footprint* fp, int* path, int* variant,
+                  int* tile_w, int* tile_h, int* box_w, int* box_h, int* lds,
+                  long long* scratch_bytes) {
+  if (!fp || w < 1 || h < 1 || (dtype != MF_U8 && dtype != MF_U16 && dtype != MF_F32))
+    return MF_ERR_INVALID_ARG;
+  mf::ImageDesc d{};
+  long long scratch = 0;
+  const int rc = mf::query_call(w, h, dtype, fp, &d, &scratch);
+  if (rc) return rc;
+  if (path) *path = d.bits ? MF_PATH_BITS : d.gs ? MF_PATH_SCRATCH : MF_PATH_LDS;
+  if (variant) *variant = d.bits - 1;
+  if (tile_w) *tile_w = d.tw;
+  if (tile_h) *tile_h = d.th;
+  if (box_w) *box_w = d.bw;
+  if (box_h) *box_h = d.bh;
+  if (lds) *lds = d.lds_bytes;
+  if (scratch_bytes) *scratch_bytes = scratch;
   return MF_OK;
 }
 

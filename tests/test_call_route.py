@@ -1,0 +1,62 @@
+"""What a call runs, told by mf_query_call without a GPU: the path of small,
+middle and large windows, shapes fitted to the image, and overrides."""
+
+import pytest
+
+import paper_2505_22938_amd as mf
+
+U8, U16, F32 = mf.MF_U8, mf.MF_U16, mf.MF_F32
+
+
+def test_paths():
+    q = lambda w, h, dt, r: mf.query_call(w, h, dt, mf.Footprint.disc(r))  # noqa: E731
+    p = q(256, 256, U8, 4)
+    assert p["path"] == "bits" and p["variant"] >= 0 and p["scratch_bytes"] == 0
+    assert (p["box_w"], p["box_h"]) == (p["tile_w"] + 8, p["tile_h"] + 8)
+    p = q(4096, 4096, U16, 32)
+    assert p["path"] == "lds" and p["variant"] == -1 and p["scratch_bytes"] == 0
+    p = q(4096, 4096, U16, 100)
+    assert p["path"] == "scratch" and p["scratch_bytes"] >= 256 * 2 * p["box_w"] * p["box_h"]
+
+
+def test_fitted_shapes_are_told():
+    """Where the default shape (mf_query_plan) is fitted to the image, the call's
+    own shape is reported."""
+    fp = mf.Footprint.disc(24)
+    assert mf.query_plan(641, 479, U16, fp)["tile_h"] == 64
+    p = mf.query_call(641, 479, U16, fp)
+    tiles = -(-641 // p["tile_w"]) * -(-479 // p["tile_h"])
+    assert p["path"] == "lds" and 88 < tiles <= 512
+    fp = mf.Footprint.disc(48)
+    assert (mf.query_plan(4096, 4096, U16, fp)["tile_w"], mf.query_plan(4096, 4096, U16, fp)["tile_h"]) \
+        == (64, 96)
+    assert mf.query_call(4096, 4096, U16, fp)["path"] == "scratch"
+    big = mf.Footprint.disc(32)
+    a, b = mf.query_plan(4096, 4096, U16, big), mf.query_call(4096, 4096, U16, big)
+    assert all(a[k] == b[k] for k in a)
+
+
+def test_tile_override_takes_calls_to_the_tile_engine():
+    fp = mf.Footprint.disc(4)
+    mf.set_tile_override(32, 16)
+    try:
+        p = mf.query_call(256, 256, U8, fp)
+        assert (p["path"], p["tile_w"], p["tile_h"]) == ("lds", 32, 16)
+    finally:
+        mf.set_tile_override(0, 0)
+    assert mf.query_call(256, 256, U8, fp)["path"] == "bits"
+
+
+def test_refused_arguments_and_windows():
+    L = mf.lib()
+    fp = mf.Footprint.disc(4)
+    none = [None] * 8
+    assert L.mf_query_call(10, 10, 7, fp.handle, *none) == -1
+    assert L.mf_query_call(0, 10, U8, fp.handle, *none) == -1
+    assert L.mf_query_call(10, 10, U8, None, *none) == -1
+    assert L.mf_query_call(10, 10, U8, fp.handle, *none) == 0
+    wide = mf.Footprint.polygon([(-150, -1), (149, -1), (149, 0), (-150, 0)])
+    for dt in (U8, U16, F32):
+        with pytest.raises(mf.MedianFilterError) as e:
+            mf.query_call(4096, 4096, dt, wide)
+        assert e.value.status == -3
