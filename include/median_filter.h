@@ -361,6 +361,18 @@ int median_filter_batched(const mf_image_desc* descs, int n, hipStream_t stream)
  * ------------------------------------------------------------------------ */
 int mf_set_tile_override(int tile_w, int tile_h);
 
+/* Bit-plane control, for measurement and tests: variant 0 .. MF_BITS_VARIANTS
+ * - 1 sends every later call whose window that variant holds to it, whatever
+ * the estimate, and the others to the tile engine; MF_BITS_OFF sends all to
+ * the tile engine (at its own shapes, unlike a tile override); MF_BITS_AUTO
+ * restores the automatic choice.  MF_ERR_INVALID_ARG otherwise.  A tile
+ * override or enabled work counters come first.  Affects later calls from
+ * every thread. */
+#define MF_BITS_VARIANTS 25
+#define MF_BITS_AUTO (-1)
+#define MF_BITS_OFF (-2)
+int mf_set_bits_override(int variant);
+
 /* Free every scratch buffer the plain, general-rank and learned filters have
  * cached (all devices and streams).  Waits for each device to go idle.  No
  * filter call may be running and no graph captured around one may be

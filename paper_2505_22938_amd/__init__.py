@@ -62,6 +62,7 @@ def lib():
         "mf_set_window_fusion": ([I], I),
         "mf_set_tile_override": ([I, I], I),
         "mf_release_scratch": ([], I),
+        "mf_set_bits_override": ([I], I),
         "mf_query_plan": ([I, I, I, P, IP, IP, IP, IP, IP], I),
         "mf_query_call": ([I, I, I, P, IP, IP, IP, IP, IP, IP, IP, ctypes.POINTER(LL)], I),
         "mf_work_counters": ([I, P], I),
@@ -403,6 +404,15 @@ def set_window_fusion(all_in_one_pass: bool):
 
 def set_tile_override(tile_w: int = 0, tile_h: int = 0):
     _check("mf_set_tile_override", lib().mf_set_tile_override(int(tile_w), int(tile_h)))
+
+
+BITS_VARIANTS, BITS_AUTO, BITS_OFF = 25, -1, -2
+
+
+def set_bits_override(variant: int = BITS_AUTO):
+    """Send calls to one bit-plane variant (those whose window it holds), or with
+    BITS_OFF all to the tile engine; BITS_AUTO restores the automatic choice."""
+    _check("mf_set_bits_override", lib().mf_set_bits_override(variant))
 
 
 def release_scratch():

@@ -36,7 +36,7 @@ PlainKernelFn pick_bits_variant(int v) {
   switch (v) {
 #define MF_BITS_CASE(I, G, P) \
   case I: return mf_bits_kernel<KT, G, P>;
-    MF_BITS_VARIANTS(MF_BITS_CASE)
+    MF_BITS_TABLE(MF_BITS_CASE)
 #undef MF_BITS_CASE
     default: return nullptr;
   }
@@ -47,7 +47,7 @@ BatchKernelFn pick_bits_batched_variant(int v) {
   switch (v) {
 #define MF_BITS_CASE(I, G, P) \
   case I: return mf_bits_batched_kernel<KT, G, P>;
-    MF_BITS_VARIANTS(MF_BITS_CASE)
+    MF_BITS_TABLE(MF_BITS_CASE)
 #undef MF_BITS_CASE
     default: return nullptr;
   }

@@ -2,6 +2,7 @@
 // variant, and the launch.
 
 #include <algorithm>
+#include <atomic>
 
 #include "mf_internal.h"
 
@@ -21,10 +22,12 @@ constexpr Variant variant() {
 
 constexpr Variant kVariants[] = {
 #define MF_BITS_ROW(I, G, P) variant<G, P>(),
-    MF_BITS_VARIANTS(MF_BITS_ROW)
+    MF_BITS_TABLE(MF_BITS_ROW)
 #undef MF_BITS_ROW
 };
 static_assert(sizeof(kVariants) / sizeof(kVariants[0]) == kBitsVariants, "variant table");
+
+std::atomic<int> g_variant{MF_BITS_AUTO};   // mf_set_bits_override
 
 // LDS: eight planes of the words, the box, the tap table
 int lds_bytes(const Variant& v, int W, int H, int es) {
@@ -73,6 +76,8 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   get_override(&tw, &th);
   // a tile shape asks for the tile engine, and the work counters count its work
   if (tw > 0 || work_counters_ptr()) return MF_ERR_UNSUPPORTED;
+  const int forced = g_variant.load();
+  if (forced == MF_BITS_OFF) return MF_ERR_UNSUPPORTED;
   const int H = (int)fp->row_lo.size(), W = (int)fp->col_lo.size(), es = elem_size(dtype);
   if (H > 64) return MF_ERR_UNSUPPORTED;   // the tap table is built by one wave, a row per lane
   // the filter's limit on windows is the tile engine's, whichever path runs:
@@ -88,6 +93,7 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   double best_us = 1e30;
   for (int i = 0; i < kBitsVariants; ++i) {
     const Variant& v = kVariants[i];
+    if (forced >= 0 && i != forced) continue;
     if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
     const double t = bits_us(v, W, H, es, lds_max, w, h);
     if (t < best_us) {
@@ -103,7 +109,7 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   // part of a round counts as that (uint8 2048 x 2048 disc 20: 327 us
   // here, tiles 345 on smooth content and 258 on noise; disc 14: 162 here,
   // the tiles more than 264).
-  if (best_us > floor_us) {
+  if (forced < 0 && best_us > floor_us) {
     ImageDesc t{};
     if (choose_plan(dtype, fp, lds_max, 33, &t, w, h, cus) == MF_OK) {
       const long long tiles = (long long)((w + t.tw - 1) / t.tw) * ((h + t.th - 1) / t.th);
@@ -149,3 +155,9 @@ int launch_bits(const ImageDesc& a, hipStream_t stream) {
 }
 
 }  // namespace mf
+
+extern "C" int mf_set_bits_override(int variant) {
+  if (variant < MF_BITS_OFF || variant >= MF_BITS_VARIANTS) return MF_ERR_INVALID_ARG;
+  mf::g_variant.store(variant);
+  return MF_OK;
+}

@@ -43,13 +43,13 @@ enum { SHAPE_DISC = 0, SHAPE_SPANS = 1 };
 
 // Bit-plane variants (bitplane.h): index, lanes per window, tap pairs per
 // lane.  A window of n pairs fits where n <= lanes * pairs.
-#define MF_BITS_VARIANTS(X) \
+#define MF_BITS_TABLE(X) \
   X(0, 1, 4) X(1, 1, 9) X(2, 1, 18) X(3, 1, 29) X(4, 1, 46) \
   X(5, 2, 32) X(6, 2, 41) X(7, 2, 50) \
   X(8, 4, 8) X(9, 4, 12) X(10, 4, 18) X(11, 4, 27) X(12, 4, 34) X(13, 4, 43) X(14, 4, 50) \
   X(15, 8, 22) X(16, 8, 30) X(17, 8, 36) X(18, 8, 42) X(19, 8, 47) \
   X(20, 16, 22) X(21, 16, 27) X(22, 16, 33) X(23, 16, 41) X(24, 16, 50)
-constexpr int kBitsVariants = 25;
+constexpr int kBitsVariants = MF_BITS_VARIANTS;
 
 // Their workgroup and tile: G lanes share a window; GX x GY sub-tiles of SX x
 // SY pixels, one word of 32 pixels (one of each sub-tile) per G threads.
