@@ -95,6 +95,10 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
     const Variant& v = kVariants[i];
     if (forced >= 0 && i != forced) continue;
     if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
+    // a launch holds fewer than 2^32 threads (half a thread to a pixel for 16
+    // lanes a window; the tiles of the tile engine take a quarter)
+    const long long tiles = (long long)((w + v.tw - 1) / v.tw) * ((h + v.th - 1) / v.th);
+    if (tiles * v.threads > 0xffffffffLL) continue;
     const double t = bits_us(v, W, H, es, lds_max, w, h);
     if (t < best_us) {
       best = i;

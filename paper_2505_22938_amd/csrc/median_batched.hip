@@ -240,7 +240,7 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
   // chip has, so one footprint takes one variant whatever the sizes.
   double px = 0;
   for (int i = 0; i < n; ++i) px += (double)descs[i].w * (double)descs[i].h;
-  const int side = (int)std::min(32768.0, std::ceil(std::sqrt(px)));
+  const int side = (int)std::min(1e9, std::ceil(std::sqrt(px)));
   for (int i = 0; i < n; ++i) {
     const mf_image_desc& e = descs[i];
     if (!e.w || !e.h) {

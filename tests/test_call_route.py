@@ -60,3 +60,15 @@ def test_refused_arguments_and_windows():
         with pytest.raises(mf.MedianFilterError) as e:
             mf.query_call(4096, 4096, dt, wide)
         assert e.value.status == -3
+
+
+def test_launches_stay_below_two_to_the_32_threads():
+    """An 8-bit image of 10 Gpixel: a window that 16 lanes share would take half a
+    thread to the pixel on bit planes."""
+    fp = mf.Footprint.disc(16)
+    p = mf.query_call(4096, 4096, U8, fp)
+    assert p["path"] == "bits"
+    threads = -(-100000 // p["tile_w"]) * -(-100000 // p["tile_h"]) * 256
+    assert threads >= 1 << 32
+    assert mf.query_call(100000, 100000, U8, fp)["path"] == "lds"
+    assert mf.query_call(100000, 100000, U8, mf.Footprint.disc(3))["path"] == "bits"
