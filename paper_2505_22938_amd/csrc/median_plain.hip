@@ -230,6 +230,7 @@ int query_call(int w, int h, int dtype, const mf_footprint* fp, ImageDesc* d, lo
   const DeviceInfo di = query_device();
   const int rc = call_plan(dtype, fp, di, w, h, d);
   if (rc) return rc;
+  trim_slot(d);
   d->tiles_x = (w + d->tw - 1) / d->tw;
   d->tiles_y = (h + d->th - 1) / d->th;
   *scratch = d->gs ? scratch_slots(*d, di) * d->slot_bytes : 0;

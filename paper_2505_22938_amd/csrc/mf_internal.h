@@ -185,6 +185,9 @@ int make_plan_br(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
 // Enumerate every valid plan (for the autotuner).
 std::vector<ImageDesc> candidate_plans(int dtype, const mf_footprint* fp, int lds_max,
                                        int imax_cap);
+// The slot of float keys sorted in LDS holds the omnigram only, a quarter of the
+// plan's layout with the words of the stable passes (done by bind_image).
+void trim_slot(ImageDesc* d);
 // Fill the per-image fields of a plan.
 void bind_image(ImageDesc* d, const void* img, int w, int h, size_t stride_bytes, int dtype,
                 const mf_footprint* fp, int boundary, int rank, const void* spans);

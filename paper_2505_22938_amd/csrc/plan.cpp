@@ -512,9 +512,15 @@ std::vector<ImageDesc> candidate_plans(int dtype, const mf_footprint* fp, int ld
   return out;
 }
 
+void trim_slot(ImageDesc* d) {
+  if (d->gs && d->kt == MF_F32 && d->off_sort)
+    d->slot_bytes = round_up(2 * (round_up(d->T, 8) + 16), 256);
+}
+
 void bind_image(ImageDesc* d, const void* img, int w, int h, size_t stride_bytes, int dtype,
                 const mf_footprint* fp, int boundary, int rank, const void* spans) {
   (void)fp;
+  trim_slot(d);
   d->img = img;
   d->w = w;
   d->h = h;

@@ -72,3 +72,13 @@ def test_launches_stay_below_two_to_the_32_threads():
     assert threads >= 1 << 32
     assert mf.query_call(100000, 100000, U8, fp)["path"] == "lds"
     assert mf.query_call(100000, 100000, U8, mf.Footprint.disc(3))["path"] == "bits"
+
+
+def test_scratch_of_float_tiles():
+    """Float tiles sorted in LDS take an omnigram of two bytes a box pixel per
+    workgroup, others the words of their sort as well (eight bytes)."""
+    for w, h, r, each in ((3840, 2160, 48, 2), (4096, 4096, 40, 2), (3840, 2160, 100, 8)):
+        p = mf.query_call(w, h, F32, mf.Footprint.disc(r))
+        box = p["box_w"] * p["box_h"]
+        assert p["path"] == "scratch" and each * box * 256 <= p["scratch_bytes"] <= \
+            (each * (box + 24) + 256) * 256, (r, p)
