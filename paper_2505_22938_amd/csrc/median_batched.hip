@@ -251,7 +251,7 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
     double us = 0;
     if ((rc = footprint_device_table(e.fp, dev, &table, nullptr)) ||
         (bits_plan(e.dtype, e.fp, di.lds_max, side, side, di.cus, &hd[i], &us) != MF_OK &&
-         (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i])))) {
+         (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i], e.w, e.h)))) {
       mf_plan_destroy(p);
       return rc;
     }

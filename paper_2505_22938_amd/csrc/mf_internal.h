@@ -171,6 +171,7 @@ int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
 // w, h, cus (image size and compute units, 0 = unknown) let the default
 // choice keep enough tiles per CU; with `spread` it is fitted to the call
 // (fit_plan, and for small images by plan_us, a shape's estimated time).
+// Without cus the image is one of a batch, whose other tiles fill the chip.
 // choose_plan_tall: the override or the tallest default shape, ignoring the
 // tuned table (bracketed tiles).
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,

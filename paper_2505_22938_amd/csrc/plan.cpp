@@ -388,8 +388,14 @@ double plan_us(const ImageDesc& c, int w, int h, int cus) {
 // of the tallest LDS shape, and the image has to give about two tiles per CU
 // (2048^2 uint16 radius 48, 512 tiles, 0.57 in 64x64 LDS tiles against 0.54
 // smooth, 0.46 against 0.37 noise; 1500x1200, 240 tiles, 0.28 against 0.34).
-// A window of radius 24 (float keys: 20) and more whose LDS shape stepped down to 64x64 for
-// four tiles per CU takes 64x96 where it gives 2.6 (2048 x 2048, 704 tiles:
+// An image whose size is known has to give fewer box pixels in all, too: small
+// and flat ones fill a part of the taller tiles (float32 radius 42, 64x128
+// against 64x48: 40000 x 32 530 us against 330, 40000 x 256 1058 against 1695;
+// batches of 1000 64-pixel squares 1.08 ms against 1.19, of 33-pixel ones
+// 1.15 against 0.62; uint16 radius 48, 64x128 against 64x96: 40000 x 48 395 us
+// against 334, 40000 x 128 536 against 664).
+// A window of radius 24 (float keys: 20) and more whose LDS shape stepped down
+// to 64x64 for four tiles per CU takes 64x96 where it gives 2.6 (2048 x 2048, 704 tiles:
 // uint16 smooth disc 24 / 32 / 48 361 / 416 / 573 -> 328 / 384 / 519 us,
 // float32 disc 20 / 24 / 32 383 / 390 / 436 -> 352 / 360 / 432; uint16 disc 20
 // 300 against 308 and on noise 276 against 297).
@@ -399,18 +405,22 @@ static void fit_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_ca
   auto tiles = [&](const ImageDesc& c) {
     return (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
   };
+  // box pixels of the whole image, c's against the default shape's
+  auto boxes = [&](const ImageDesc& c) {
+    return w > 0 && h > 0 ? (double)(tiles(c) * c.T) / (double)(tiles(*d) * d->T) : 0.0;
+  };
   if (d->gs || std::min(d->nrows, d->ncols) <= 33) return;
   ImageDesc c{}, tall{};
   if (best_gs_plan(dtype, fp, lds_max, &c) == MF_OK && (dtype != MF_F32 || c.off_sort) &&
       default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), 0, 0, 0, &tall) == MF_OK &&
       (double)tall.T * c.tw * c.th > 1.05 * (double)c.T * tall.tw * tall.th &&
-      (!sized || tiles(c) * 10 >= 19LL * cus)) {
+      1.05 * boxes(c) <= 1.0 && (!sized || tiles(c) * 10 >= 19LL * cus)) {
     *d = c;
     return;
   }
   if (sized && d->tw == 64 && d->th == 64 && std::min(d->nrows, d->ncols) > (dtype == MF_F32 ? 40 : 46) &&
       make_plan(dtype, fp, lds_max, 64, 96, &c) == MF_OK && c.imax <= imax_cap &&
-      tiles(c) * 10 >= 26LL * cus)
+      boxes(c) < 1.0 && tiles(c) * 10 >= 26LL * cus)
     *d = c;
 }
 

@@ -82,3 +82,23 @@ def test_scratch_of_float_tiles():
         box = p["box_w"] * p["box_h"]
         assert p["path"] == "scratch" and each * box * 256 <= p["scratch_bytes"] <= \
             (each * (box + 24) + 256) * 256, (r, p)
+
+
+def test_flat_images_keep_the_shorter_tiles():
+    """A middle window takes the tall global-scratch tiles only where the image
+    gives them fewer box pixels to sort."""
+    q = lambda w, h, dt, r: mf.query_call(w, h, dt, mf.Footprint.disc(r))["path"]  # noqa: E731
+    for dt, r in ((F32, 42), (U16, 48), (U8, 48)):
+        assert q(40000, 32, dt, r) == "lds" and q(40000, 48, dt, r) == "lds"
+        assert q(40000, 256, dt, r) == "scratch" and q(4096, 4096, dt, r) == "scratch"
+    assert q(40000, 96, U16, 46) == "lds" and q(40000, 128, U16, 46) == "scratch"
+
+
+@pytest.mark.gpu
+def test_batches_of_small_images_keep_the_shorter_tiles():
+    torch = pytest.importorskip("torch")
+    for side, scratch in ((16, False), (33, False), (128, True), (256, True)):
+        img = torch.zeros((side, side), dtype=torch.float32, device="cuda")
+        plan = mf.BatchPlan([(img, torch.empty_like(img), mf.Footprint.disc(42), "clamp")])
+        assert (plan.info()["scratch_bytes"] > 0) == scratch, side
+        plan.close()
