@@ -91,7 +91,6 @@ def test_flat_images_keep_the_shorter_tiles():
     for dt, r in ((F32, 42), (U16, 48), (U8, 48)):
         assert q(40000, 32, dt, r) == "lds" and q(40000, 48, dt, r) == "lds"
         assert q(40000, 256, dt, r) == "scratch" and q(4096, 4096, dt, r) == "scratch"
-    assert q(40000, 96, U16, 46) == "lds" and q(40000, 128, U16, 46) == "scratch"
 
 
 @pytest.mark.gpu
