@@ -108,16 +108,20 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   if (best < 0) return MF_ERR_UNSUPPORTED;
   const double floor_us = tile_us(dtype, w, h);
   // Not clearly faster: against the tile plan, whose estimate is for smooth
-  // content and whole rounds.  Noise takes up to a quarter less, and many
-  // rounds drift apart, so over more than two the line lies a tenth lower and
-  // part of a round counts as that (uint8 2048 x 2048 disc 20: 327 us
-  // here, tiles 345 on smooth content and 258 on noise; disc 14: 162 here,
-  // the tiles more than 264).
+  // content, whole rounds and walks as under large windows.  Noise takes up to a
+  // quarter less, and many rounds drift apart, so over more than two the line
+  // lies a tenth lower and part of a round counts as that (uint8 2048 x 2048
+  // disc 20: 327 us here, tiles 345 on smooth content and 258 on noise; disc 14:
+  // 162 here, the tiles more than 264).  Images of two values take the tiles two
+  // to twelve times as long as smooth ones and no longer here (uint8 2077 x 1741
+  // disc 20 309 us against 654, a checkerboard of 2465 x 2738 disc 19 535 against
+  // 6440), so the line is not moved to where noise alone would put it.
   if (forced < 0 && best_us > floor_us) {
+    constexpr int kManyTaps = 1 << 20;
     ImageDesc t{};
     if (choose_plan(dtype, fp, lds_max, 33, &t, w, h, cus) == MF_OK) {
       const long long tiles = (long long)((w + t.tw - 1) / t.tw) * ((h + t.th - 1) / t.th);
-      const double tus = plan_us(t, w, h, cus) *
+      const double tus = plan_us(t, kManyTaps, w, h, cus) *
                          (tiles > 2LL * cus ? 0.9 * (double)tiles / (double)((tiles + cus - 1) / cus * cus)
                                             : 1.0);
       if (best_us > std::max(floor_us, tus)) return MF_ERR_UNSUPPORTED;

@@ -241,6 +241,10 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
   double px = 0;
   for (int i = 0; i < n; ++i) px += (double)descs[i].w * (double)descs[i].h;
   const int side = (int)std::min(1e9, std::ceil(std::sqrt(px)));
+  // Fitted (taller) tiles where the batch gives about two of them per CU, as for
+  // a plain call: a batch of few tiles lasts its longest one (float32 62 x 92
+  // radius 34 238 us in one 64x128 tile, 170 in two of 64x80).
+  const bool many = px >= 1.9 * di.cus * 64 * 128;
   for (int i = 0; i < n; ++i) {
     const mf_image_desc& e = descs[i];
     if (!e.w || !e.h) {
@@ -251,7 +255,7 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
     double us = 0;
     if ((rc = footprint_device_table(e.fp, dev, &table, nullptr)) ||
         (bits_plan(e.dtype, e.fp, di.lds_max, side, side, di.cus, &hd[i], &us) != MF_OK &&
-         (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i], e.w, e.h)))) {
+         (rc = choose_plan(e.dtype, e.fp, di.lds_max, kMaxItems, &hd[i], e.w, e.h, 0, many)))) {
       mf_plan_destroy(p);
       return rc;
     }

@@ -10,6 +10,7 @@
 // outside every box (the omnigram's padding location).
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -360,19 +361,26 @@ static int default_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
 
 // Estimated time in microseconds of a tile plan on a w x h image whose tiles
 // run one per CU in rounds: a fixed part, the box (load and sort) and, for
-// the tile's pixels, walks in proportion to the box.  Measured on smooth
-// uint16 content (estimate), us a round: 641 x 479 disc 24, 64x64 / 64x32 /
-// 32x48 / 32x32 / 16x16 tiles 116 / 75 / 59 / 46 / 28 (96 / 58 / 50 / 41 /
-// 32); disc 64, 64x64 (global scratch) / 64x32 / 32x48 / 16x16 227 / 151 /
-// 127 / 77 (254 / 146 / 122 / 72); 1500 x 1200 disc 32, 64x64 / 64x128 109 /
-// 254 (119 / 257).  float32 log-normal 641 x 479: disc 24, 64x64 / 16x16
-// 103 / 41 (98 / 44), disc 64, 64x64 / 32x32 (global scratch) / 16x16 270 /
-// 191 / 106 (326 / 197 / 103).
-double plan_us(const ImageDesc& c, int w, int h, int cus) {
+// the tile's pixels, walks in proportion to the box and, under windows of few
+// taps, whose members lie far apart in it, to N^-1/2 and more.  Measured on
+// smooth uint16 content (estimate), us a round: 641 x 479 disc 24, 64x64 /
+// 64x32 / 32x48 / 32x32 / 16x16 tiles 116 / 75 / 59 / 46 / 28 (96 / 58 / 50 /
+// 41 / 32); disc 64, 64x64 (global scratch) / 64x32 / 32x48 / 16x16 227 / 151
+// / 127 / 77 (254 / 146 / 122 / 72); 1500 x 1200 disc 32, 64x64 / 64x128 109 /
+// 254 (119 / 257); one round of disc 2 64x32 / 32x96 104 / 173 (95 / 178), of
+// disc 8 64x64 / 64x96 89 / 133 (94 / 164).  float32 log-normal 641 x 479: disc
+// 24, 64x64 / 16x16 103 / 41 (98 / 44), disc 64, 64x64 / 32x32 (global
+// scratch) / 16x16 270 / 191 / 106 (326 / 197 / 103); one round of disc 13,
+// 64x64 / 64x112 / 64x128 100 / 160 / 188 (81 / 139 / 161), of disc 2, 64x32 /
+// 64x64 / 64x112 116 / 298 / 738 (95 / 260 / 694).
+double plan_us(const ImageDesc& c, int taps, int w, int h, int cus) {
   const bool f32 = c.kt == MF_F32;
   const double fixed = f32 ? 30.0 : 22.0;
   const double key = f32 ? (c.gs && !c.off_sort ? 6.0 : 3.4) : 2.2;
-  const double walk = (f32 ? 0.5 : 0.9) * 64.0 / (c.tw * c.segs);
+  const double n = std::max(1, taps);
+  const double walk = std::max(f32 ? 0.5 : 0.9,
+                               (f32 ? 15.5 * (1.0 + 20.0 / n) : 30.0 * (1.0 + 8.0 / n)) / std::sqrt(n)) *
+                      64.0 / (c.tw * c.segs);
   const double T = c.T * 1e-3, px = c.tw * c.th * 1e-3;
   const long long tiles = (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
   return (fixed + key * T + walk * T * px) * (double)((tiles + cus - 1) / cus);
@@ -439,14 +447,14 @@ static void spread_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
   if (tiles * 20 >= 4LL * cus * 19) return;
   static const int tws[] = {64, 48, 32, 16};
   static const int ths[] = {128, 112, 96, 80, 64, 48, 32, 16};
-  double best = 0.92 * plan_us(*d, w, h, cus);
+  double best = 0.92 * plan_us(*d, fp->taps, w, h, cus);
   for (int tw : tws)
     for (int th : ths) {
       ImageDesc c{};
       if (plan_shape(dtype, fp, lds_max, imax_cap, tw, th, &c) != MF_OK) continue;
       const long long n = (long long)((w + tw - 1) / tw) * ((h + th - 1) / th);
       if (n > 2LL * cus) continue;
-      const double us = plan_us(c, w, h, cus);
+      const double us = plan_us(c, fp->taps, w, h, cus);
       if (us < best) {
         best = us;
         *d = c;
@@ -461,7 +469,7 @@ int lds_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w
     for (int th : {128, 112, 96, 80, 64, 48, 32, 16, 8}) {
       ImageDesc c{};
       if (make_plan(dtype, fp, lds_max, tw, th, &c) != MF_OK || c.imax > imax_cap) continue;
-      const double us = plan_us(c, w, h, cus);
+      const double us = plan_us(c, fp->taps, w, h, cus);
       if (us < best) {
         best = us;
         *d = c;

@@ -95,9 +95,39 @@ def test_flat_images_keep_the_shorter_tiles():
 
 @pytest.mark.gpu
 def test_batches_of_small_images_keep_the_shorter_tiles():
+    """So do batches of few tiles, which last their longest one."""
     torch = pytest.importorskip("torch")
-    for side, scratch in ((16, False), (33, False), (128, True), (256, True)):
-        img = torch.zeros((side, side), dtype=torch.float32, device="cuda")
-        plan = mf.BatchPlan([(img, torch.empty_like(img), mf.Footprint.disc(42), "clamp")])
-        assert (plan.info()["scratch_bytes"] > 0) == scratch, side
+    fp = mf.Footprint.disc(42)
+    for side, n, scratch in ((16, 20000, False), (33, 4500, False), (128, 300, True), (256, 80, True),
+                             (128, 20, False), (256, 1, False)):
+        img = torch.zeros((n, side, side), dtype=torch.float32, device="cuda")
+        out = torch.empty_like(img)
+        plan = mf.BatchPlan([(img[i], out[i], fp, "clamp") for i in range(n)])
+        assert (plan.info()["scratch_bytes"] > 0) == scratch, (side, n)
         plan.close()
+
+
+def test_shapes_of_small_windows_on_middle_images():
+    """Walks under small windows grow with the box, so few taps keep low tiles:
+    float32 radius 2 on 721 x 2197 takes 389 us in 64 x 32 tiles and 738 in one
+    round of 64 x 112."""
+    mf.set_bits_override(mf.BITS_OFF)
+    try:
+        for w, h, dt, r in ((721, 2197, F32, 2), (825, 1576, F32, 2), (724, 2170, F32, 3),
+                            (2379, 675, F32, 11), (1640, 1124, F32, 13), (2125, 574, U8, 2),
+                            (929, 977, U16, 1)):
+            fp = mf.Footprint.disc(r)
+            p, d = mf.query_call(w, h, dt, fp), mf.query_plan(w, h, dt, fp)
+            assert p["tile_h"] <= d["tile_h"], (w, h, dt, r, p, d)
+        p = mf.query_call(641, 479, U16, mf.Footprint.disc(24))
+        assert p["tile_w"] * p["tile_h"] < 64 * 64
+    finally:
+        mf.set_bits_override(mf.BITS_AUTO)
+
+
+def test_line_between_the_paths():
+    """The largest disc on bit planes at 4096 x 4096."""
+    q = lambda w, h, dt, r: mf.query_call(w, h, dt, mf.Footprint.disc(r))["path"]  # noqa: E731
+    for dt, r in ((U8, 16), (U16, 12), (F32, 10)):
+        assert q(4096, 4096, dt, r) == "bits" and q(4096, 4096, dt, r + 6) == "lds"
+    assert q(641, 479, U8, 16) == "bits" and q(300, 300, U16, 24) == "lds"
