@@ -71,7 +71,7 @@ double tile_us(int dtype, long long w, long long h) {
 int bits_threads(int v) { return kVariants[v].threads; }
 
 int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d,
-              double* us) {
+              double* us, ImageDesc* tile_plan) {
   int tw = 0, th = 0;
   get_override(&tw, &th);
   // a tile shape asks for the tile engine, and the work counters count its work
@@ -124,7 +124,10 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
       const double tus = plan_us(t, kManyTaps, w, h, cus) *
                          (tiles > 2LL * cus ? 0.9 * (double)tiles / (double)((tiles + cus - 1) / cus * cus)
                                             : 1.0);
-      if (best_us > std::max(floor_us, tus)) return MF_ERR_UNSUPPORTED;
+      if (best_us > std::max(floor_us, tus)) {
+        if (tile_plan) *tile_plan = t;
+        return MF_ERR_UNSUPPORTED;
+      }
     }
   }
   if (us) *us = best_us;
@@ -145,6 +148,16 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   d->limit = (int)fp->limit;
   d->lds_bytes = lds_bytes(v, W, H, es);
   return MF_OK;
+}
+
+int call_plan(int dtype, const mf_footprint* fp, const DeviceInfo& di, int w, int h, ImageDesc* d) {
+  ImageDesc t{};
+  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, d, nullptr, &t) == MF_OK) return MF_OK;
+  if (t.tw) {
+    *d = t;
+    return MF_OK;
+  }
+  return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus);
 }
 
 int launch_bits(const ImageDesc& a, hipStream_t stream) {

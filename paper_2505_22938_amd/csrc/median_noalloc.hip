@@ -79,9 +79,7 @@ extern "C" int median_filter_noalloc(const void* img, int w, int h, size_t strid
   if ((rc = scratch_ptr(dev, &base))) return rc;
 
   ImageDesc a{};
-  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, &a) != MF_OK &&
-      (rc = choose_plan(dtype, fp, di.lds_max, 33, &a, w, h, di.cus)))
-    return rc;
+  if ((rc = call_plan(dtype, fp, di, w, h, &a))) return rc;
   const size_t nspan = footprint_span_table_len(fp) / 2;
   if (nspan > (size_t)kMaxSpans || nspan * sizeof(short2) > kSpanRegion)
     return MF_ERR_SCRATCH_LIMIT;

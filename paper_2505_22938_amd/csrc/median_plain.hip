@@ -150,13 +150,6 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
   return MF_OK;
 }
 
-// The plan of a plain call: bit planes or tiles fitted to the image.
-static int call_plan(int dtype, const mf_footprint* fp, const DeviceInfo& di, int w, int h,
-                     ImageDesc* d) {
-  if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, d) == MF_OK) return MF_OK;
-  return choose_plan(dtype, fp, di.lds_max, 33, d, w, h, di.cus);
-}
-
 int launch_plain(const void* img, int w, int h, size_t stride_bytes, int dtype,
                  const mf_footprint* fp, int boundary, int rank, void* out, hipStream_t stream) {
   int dev = 0;

@@ -268,11 +268,14 @@ int launch_fitted(ImageDesc a, int dtype, const mf_footprint* fp, int w, int h, 
   bind(&l);
   return launch_with_plan(l, dev, di, stream);
 }
+// The plan of a plain call: bit planes, or tiles fitted to the image.
+int call_plan(int dtype, const mf_footprint* fp, const DeviceInfo& di, int w, int h, ImageDesc* d);
 // Bit-plane path: plan for a window it takes (MF_ERR_UNSUPPORTED otherwise),
 // kernel, and launch with a complete plan.
-// us (optional): the estimated time of the image.
+// us (optional): the estimated time of the image.  tile_plan (optional): set to
+// choose_plan's where that was found the faster.
 int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int cus, ImageDesc* d,
-              double* us = nullptr);
+              double* us = nullptr, ImageDesc* tile_plan = nullptr);
 PlainKernelFn pick_bits_u8(int v);
 PlainKernelFn pick_bits_u16(int v);
 PlainKernelFn pick_bits_f32(int v);

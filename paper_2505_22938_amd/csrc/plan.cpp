@@ -251,13 +251,12 @@ int best_gs_plan(int dtype, const mf_footprint* fp, int lds_max, ImageDesc* d) {
   static const int tws[] = {64, 56, 54, 48, 32, 16, 8};
   static const int ths[] = {128, 112, 96, 80, 64, 56, 54, 48, 32, 16, 8};
   double best = 1e300;
-  ImageDesc pick{};
+  ImageDesc c{};   // (make_plan_gs sets the same fields for every shape)
   bool found = false;
   for (int w : tws) {
     const int segs = 64 / w;
     if (w * segs < 48) continue;
     for (int h : ths) {
-      ImageDesc c{};
       if (make_plan_gs(dtype, fp, lds_max, w, h, &c) != MF_OK) continue;
       const int bands = (h + c.band_rows - 1) / c.band_rows;
       if (bands * 2 < kWaves * segs && h > kWaves) continue;
@@ -265,14 +264,12 @@ int best_gs_plan(int dtype, const mf_footprint* fp, int lds_max, ImageDesc* d) {
                          (dtype == MF_F32 && !c.off_sort ? kGlobalSort : 1.0);
       if (amp < best) {
         best = amp;
-        pick = c;
+        *d = c;
         found = true;
       }
     }
   }
-  if (!found) return MF_ERR_UNSUPPORTED;
-  *d = pick;
-  return MF_OK;
+  return found ? MF_OK : MF_ERR_UNSUPPORTED;
 }
 
 // Tallest output tile for the default choice, by the window's extent e (its
@@ -305,10 +302,11 @@ static int default_th_cap(const mf_footprint* fp) {
 // a kept 64-wide LDS shape steps down in height (not below 64) while the
 // image would have fewer tiles than that (fewer tiles per CU than needed
 // to balance tiles of uneven cost).
+// tall_gs: best_gs_plan's shape, null if there is none.
 static int default_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int th_cap,
-                        int w, int h, long long fill_tiles, ImageDesc* d) {
-  ImageDesc gs{};
-  const bool have_gs = best_gs_plan(dtype, fp, lds_max, &gs) == MF_OK;
+                        int w, int h, long long fill_tiles, const ImageDesc* tall_gs, ImageDesc* d) {
+  const bool have_gs = tall_gs != nullptr;
+  ImageDesc gs = have_gs ? *tall_gs : ImageDesc{};
   // a 64-wide global-scratch plan steps down in height (not below 64) while
   // the image would give fewer tiles than CUs (fill_tiles / 4): on 1024^2
   // uint16 natural-like, radius 56/64, 64x64 tiles take 0.22/0.28 ms against
@@ -408,7 +406,7 @@ double plan_us(const ImageDesc& c, int taps, int w, int h, int cus) {
 // float32 disc 20 / 24 / 32 383 / 390 / 436 -> 352 / 360 / 432; uint16 disc 20
 // 300 against 308 and on noise 276 against 297).
 static void fit_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h,
-                     int cus, ImageDesc* d) {
+                     int cus, const ImageDesc* gs, ImageDesc* d) {
   const bool sized = w > 0 && h > 0 && cus > 0;
   auto tiles = [&](const ImageDesc& c) {
     return (long long)((w + c.tw - 1) / c.tw) * ((h + c.th - 1) / c.th);
@@ -419,11 +417,11 @@ static void fit_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_ca
   };
   if (d->gs || std::min(d->nrows, d->ncols) <= 33) return;
   ImageDesc c{}, tall{};
-  if (best_gs_plan(dtype, fp, lds_max, &c) == MF_OK && (dtype != MF_F32 || c.off_sort) &&
-      default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), 0, 0, 0, &tall) == MF_OK &&
-      (double)tall.T * c.tw * c.th > 1.05 * (double)c.T * tall.tw * tall.th &&
-      1.05 * boxes(c) <= 1.0 && (!sized || tiles(c) * 10 >= 19LL * cus)) {
-    *d = c;
+  if (gs && (dtype != MF_F32 || gs->off_sort) && 1.05 * boxes(*gs) <= 1.0 &&
+      (!sized || tiles(*gs) * 10 >= 19LL * cus) &&
+      default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), 0, 0, 0, gs, &tall) == MF_OK &&
+      (double)tall.T * gs->tw * gs->th > 1.05 * (double)gs->T * tall.tw * tall.th) {
+    *d = *gs;
     return;
   }
   if (sized && d->tw == 64 && d->th == 64 && std::min(d->nrows, d->ncols) > (dtype == MF_F32 ? 40 : 46) &&
@@ -448,9 +446,9 @@ static void spread_plan(int dtype, const mf_footprint* fp, int lds_max, int imax
   static const int tws[] = {64, 48, 32, 16};
   static const int ths[] = {128, 112, 96, 80, 64, 48, 32, 16};
   double best = 0.92 * plan_us(*d, fp->taps, w, h, cus);
+  ImageDesc c{};
   for (int tw : tws)
     for (int th : ths) {
-      ImageDesc c{};
       if (plan_shape(dtype, fp, lds_max, imax_cap, tw, th, &c) != MF_OK) continue;
       const long long n = (long long)((w + tw - 1) / tw) * ((h + th - 1) / th);
       if (n > 2LL * cus) continue;
@@ -487,10 +485,12 @@ int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, Im
       plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d) == MF_OK)
     return MF_OK;
   const bool sized = w > 0 && h > 0 && cus > 0;
+  ImageDesc best_gs{};
+  const ImageDesc* gs = best_gs_plan(dtype, fp, lds_max, &best_gs) == MF_OK ? &best_gs : nullptr;
   const int rc = default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), w, h,
-                              sized ? 4LL * cus : 0, d);
+                              sized ? 4LL * cus : 0, gs, d);
   if (rc == MF_OK && spread) {
-    fit_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+    fit_plan(dtype, fp, lds_max, imax_cap, w, h, cus, gs, d);
     if (sized) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
   }
   return rc;
@@ -501,7 +501,9 @@ int choose_plan_tall(int dtype, const mf_footprint* fp, int lds_max, int imax_ca
   int tw = 0, th = 0;
   get_override(&tw, &th);
   if (tw > 0) return plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d);
-  return default_plan(dtype, fp, lds_max, imax_cap, 128, 0, 0, 0, d);
+  ImageDesc gs{};
+  const bool have_gs = best_gs_plan(dtype, fp, lds_max, &gs) == MF_OK;
+  return default_plan(dtype, fp, lds_max, imax_cap, 128, 0, 0, 0, have_gs ? &gs : nullptr, d);
 }
 
 std::vector<ImageDesc> candidate_plans(int dtype, const mf_footprint* fp, int lds_max,
