@@ -195,12 +195,10 @@ void mf_plan_destroy(mf_plan* p) {
   delete p;
 }
 
-int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_path,
-                   mf_plan** out) {
+// fitted: tiles that choose_plan fits to the images, which may take scratch
+// where the default ones take none.
+static int create_plan(const mf_image_desc* descs, int n, bool fitted, mf_plan** out) {
   using namespace mf;
-  if (!out || n < 0 || (n > 0 && !descs)) return MF_ERR_INVALID_ARG;
-  *out = nullptr;
-  if (tune_cache_path && *tune_cache_path) (void)tune_cache_load(tune_cache_path);
   // argument checks, including aliasing between any output and any buffer
   std::vector<size_t> span(n);
   for (int i = 0; i < n; ++i) {
@@ -244,7 +242,7 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
   // Fitted (taller) tiles where the batch gives about two of them per CU, as for
   // a plain call: a batch of few tiles lasts its longest one (float32 62 x 92
   // radius 34 238 us in one 64x128 tile, 170 in two of 64x80).
-  const bool many = px >= 1.9 * di.cus * 64 * 128;
+  const bool many = fitted && px >= 1.9 * di.cus * 64 * 128;
   for (int i = 0; i < n; ++i) {
     const mf_image_desc& e = descs[i];
     if (!e.w || !e.h) {
@@ -347,6 +345,19 @@ int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_pat
                               g.lds_bytes);
   *out = p;
   return MF_OK;
+}
+
+int mf_plan_create(const mf_image_desc* descs, int n, const char* tune_cache_path,
+                   mf_plan** out) {
+  if (!out || n < 0 || (n > 0 && !descs)) return MF_ERR_INVALID_ARG;
+  *out = nullptr;
+  if (tune_cache_path && *tune_cache_path) (void)mf::tune_cache_load(tune_cache_path);
+  int rc = create_plan(descs, n, true, out);
+  if (rc == MF_ERR_NOMEM) {   // the default tiles take less scratch
+    (void)hipGetLastError();
+    rc = create_plan(descs, n, false, out);
+  }
+  return rc;
 }
 
 int mf_plan_launch(mf_plan* p, hipStream_t stream) {
