@@ -209,7 +209,8 @@ int median_filter_noalloc(const void* img, int w, int h, size_t stride_bytes, in
  *
  * median_filter_ranks writes `nouts` planes (1..MF_MAX_RANK_OUTPUTS) from
  * one pass: each tile's box is loaded and sorted once, then its bands run
- * once per plane.  Plane q goes to outs[q].out (same shape and stride as
+ * once per plane (constant ranks of a window that runs on bit planes: a
+ * launch per plane).  Plane q goes to outs[q].out (same shape and stride as
  * img) and holds, at pixel (x, y), the window element of zero-based rank
  *   rank_map[y * (rank_map_stride_bytes / 4) + x], clamped to [0, N - 1],
  *   where outs[q].rank_map is not NULL (device int32 plane, w x h, stride a
@@ -254,7 +255,9 @@ int median_filter_rank_map(const void* img, int w, int h, size_t stride_bytes, i
  * of the window outs[q].footprint (N_q taps) centred there.  Every
  * footprint must be non-NULL (MF_ERR_INVALID_ARG).
  *
- * The windows are grouped into passes: in decreasing order of the box
+ * Windows of constant rank that median_filter_rank would run on bit planes are
+ * queued first, each by itself.  The others are grouped into passes: in
+ * decreasing order of the box
  * their own single-window plan loads (T_q pixels, for tiles of P_q), window
  * q joins the current pass, whose first window's box has T_0 pixels, while
  * (T_q / P_q) * N_q >= 0.25 * (T_0 - T_q), else it starts a new pass (a
@@ -295,17 +298,18 @@ int mf_set_window_fusion(int all);
  *
  * mf_plan_create validates every entry (as median_filter does, plus no
  * output may overlap any input or other output: MF_ERR_ALIAS), plans each
- * image exactly as median_filter would (the tuned tile shape for its dtype
- * and footprint when the tuned table has one -- loaded first from
- * `tune_cache_path` if not NULL -- else the default choice), groups all
- * tiles by kernel variant (dtype, footprint form, register capacity or
- * global scratch), orders each group longest-estimated-first, and allocates
- * the device tables: a descriptor per image, the tile queue, two counters
- * per group and, if some image needs it, global scratch; it also creates up
- * to three streams and four events of its own (default priority).  The plan
- * keeps the buffer pointers of `descs` (the device images themselves are
- * not copied): they must stay valid for every launch.  The footprints must
- * outlive the plan.  Synchronous.
+ * image (bit planes or tiles by median_filter's rule for one square image of
+ * the whole batch's pixels; for tiles the tuned shape for its dtype and
+ * footprint when the tuned table has one -- loaded first from
+ * `tune_cache_path` if not NULL -- else the default choice, not stepped down
+ * for the image's own size), groups all tiles by kernel variant (dtype,
+ * footprint form, register capacity or global scratch, or bit-plane variant),
+ * orders each group longest-estimated-first, and allocates the device tables:
+ * a descriptor per image, the tile queue, two counters per group and, if some
+ * image needs it, global scratch; it also creates up to three streams and four
+ * events of its own (default priority).  The plan keeps the buffer pointers of
+ * `descs` (the device images themselves are not copied): they must stay valid
+ * for every launch.  The footprints must outlive the plan.  Synchronous.
  *
  * mf_plan_launch queues one kernel per group: global-scratch groups run a
  * persistent grid (CUs x occupancy workgroups popping tiles; the last one
@@ -402,9 +406,12 @@ int mf_work_counters(int enable, unsigned long long* out10);
  * median_filter (device buffers; out is overwritten), `reps` timed runs per
  * shape after one warm-up, on `stream` (synchronous: returns when timing
  * is done).  The fastest shape is recorded in the library's tuned-shape
- * table, which later plain calls and batched plans consult for the same
- * dtype and footprint.  Outputs (any may be NULL): the shape and its mean
- * time in milliseconds.
+ * table, which later calls and batched plans consult for the same dtype and
+ * footprint where they run tiles: the table does not keep a window from the
+ * bit planes, so a call on an image where it runs there takes another time
+ * than the one returned.  The shape that an untuned call fits to this image is
+ * among those timed; a recorded one is not fitted to other images.  Outputs
+ * (any may be NULL): the shape and its mean time in milliseconds.
  * ------------------------------------------------------------------------ */
 int mf_autotune(const void* img, int w, int h, size_t stride_bytes, int dtype,
                 const mf_footprint* fp, int boundary, void* out, hipStream_t stream, int reps,
@@ -417,9 +424,11 @@ int mf_autotune(const void* img, int w, int h, size_t stride_bytes, int dtype,
  * `stream` after one warm-up) with that footprint's recorded shape and
  * with the default shape, and keeps in the tuned-shape table whichever
  * makes the whole batch faster; footprints without a recorded shape are
- * left alone.  Synchronous.  Outputs (any may be NULL): batch time before
- * and after (ms), and the number of footprints whose recorded shape was
- * dropped.  Later plain calls and plans use the table as left. */
+ * left alone, and so are those that the batch runs on bit planes.  At last the
+ * batch is timed without any of the shapes kept.  Synchronous.  Outputs (any
+ * may be NULL): batch time before and after (ms), and the number of footprints
+ * whose recorded shape was dropped.  Later plain calls and plans use the table
+ * as left. */
 int mf_plan_autotune(const mf_image_desc* descs, int n, hipStream_t stream, int reps,
                      float* before_ms, float* after_ms, int* dropped);
 

@@ -127,6 +127,13 @@ double tile_cost(const ImageDesc& d) {
          (d.gs ? (double)d.T * passes * 8.0 : 0.0);
 }
 
+// Side of a square of the whole batch's pixels (px).
+int batch_side(const mf_image_desc* descs, int n, double* px) {
+  *px = 0;
+  for (int i = 0; i < n; ++i) *px += (double)descs[i].w * (double)descs[i].h;
+  return (int)std::min(1e9, std::ceil(std::sqrt(*px)));
+}
+
 // tile_cost of a tile that takes a compute unit one microsecond (disc 32
 // uint16, 64 x 64 tiles: 1.45 M, 78 us), for bit-plane tiles.
 constexpr double kCostPerUs = 18600.0;
@@ -237,8 +244,7 @@ static int create_plan(const mf_image_desc* descs, int n, bool fitted, mf_plan**
   // plain call on an image of the whole batch's pixels: that is the work the
   // chip has, so one footprint takes one variant whatever the sizes.
   double px = 0;
-  for (int i = 0; i < n; ++i) px += (double)descs[i].w * (double)descs[i].h;
-  const int side = (int)std::min(1e9, std::ceil(std::sqrt(px)));
+  const int side = batch_side(descs, n, &px);
   // Fitted (taller) tiles where the batch gives about two of them per CU, as for
   // a plain call: a batch of few tiles lasts its longest one (float32 62 x 92
   // radius 34 238 us in one 64x128 tile, 170 in two of 64x80).
@@ -471,9 +477,21 @@ int mf_plan_autotune(const mf_image_desc* descs, int n, hipStream_t stream, int 
     double cost;
   };
   std::vector<Grp> grps;
+  int dev = 0;
+  DeviceInfo di;
+  if (hipGetDevice(&dev) != hipSuccess || device_info(dev, &di) != MF_OK) {
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    return MF_ERR_HIP;
+  }
+  double px = 0;
+  const int side = batch_side(descs, n, &px);
   for (int i = 0; i < n; ++i) {
     const mf_image_desc& e = descs[i];
     if (!e.fp || !e.w || !e.h) continue;
+    // the shapes recorded for windows on bit planes change nothing here
+    ImageDesc bits{};
+    if (bits_plan(e.dtype, e.fp, di.lds_max, side, side, di.cus, &bits) == MF_OK) continue;
     const double c = (double)e.w * e.h * (2.0 * (e.fp->dx_max - e.fp->dx_min + 1) + 160.0);
     const std::string k = tune_key(e.dtype, e.fp);
     bool found = false;
@@ -502,6 +520,28 @@ int mf_plan_autotune(const mf_image_desc* descs, int n, hipStream_t stream, int 
       ++ndrop;
     } else {
       record_tuned_shape(g.dtype, g.fp, tw, th, 0.0);
+    }
+  }
+  // shapes that each change little on their own may lose together: the default
+  // ones for what is left, all at once
+  struct Kept {
+    const Grp* g;
+    int tw, th;
+  };
+  std::vector<Kept> kept;
+  for (const Grp& g : grps) {
+    Kept k{&g, 0, 0};
+    if (!rc && tuned_shape(g.dtype, g.fp, &k.tw, &k.th)) kept.push_back(k);
+  }
+  if (kept.size() > 1) {
+    for (const Kept& k : kept) erase_tuned_shape(k.g->dtype, k.g->fp);
+    float t = 0;
+    rc = time_batch(&t);
+    if (!rc && t < best) {
+      best = t;
+      ndrop += (int)kept.size();
+    } else {
+      for (const Kept& k : kept) record_tuned_shape(k.g->dtype, k.g->fp, k.tw, k.th, 0.0);
     }
   }
   (void)hipEventDestroy(e0);

@@ -355,7 +355,16 @@ int mf_autotune(const void* img, int w, int h, size_t stride_bytes, int dtype,
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return MF_ERR_HIP;
   float best = 1e30f;
   int btw = 0, bth = 0;
-  for (mf::ImageDesc d : mf::candidate_plans(dtype, fp, di.lds_max, 33)) {
+  // the shape an untuned call takes on this image is a candidate too, so that a
+  // recorded one is no slower
+  std::vector<mf::ImageDesc> cand = mf::candidate_plans(dtype, fp, di.lds_max, 33);
+  mf::ImageDesc own{};
+  if (mf::untuned_plan(dtype, fp, di.lds_max, 33, &own, w, h, di.cus, true) == MF_OK) {
+    bool seen = false;
+    for (const mf::ImageDesc& c : cand) seen = seen || (c.tw == own.tw && c.th == own.th);
+    if (!seen) cand.push_back(own);
+  }
+  for (mf::ImageDesc& d : cand) {
     mf::bind_image(&d, img, w, h, stride_bytes, dtype, fp, boundary, (fp->taps - 1) / 2, table);
     d.out = out;
     if (mf::launch_with_plan(d, dev, di, stream) != MF_OK) continue;   // warm-up

@@ -176,6 +176,9 @@ int make_plan_gs(int dtype, const mf_footprint* fp, int lds_max, int tw, int th,
 // tuned table (bracketed tiles).
 int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
                 int w = 0, int h = 0, int cus = 0, bool spread = true);
+// choose_plan without the override and the tuned table.
+int untuned_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
+                 int w, int h, int cus, bool spread);
 double plan_us(const ImageDesc& c, int taps, int w, int h, int cus);
 int choose_plan_tall(int dtype, const mf_footprint* fp, int lds_max, int imax_cap,
                      ImageDesc* d);

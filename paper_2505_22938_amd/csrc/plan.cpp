@@ -476,14 +476,8 @@ int lds_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w
   return best < 1e300 ? MF_OK : MF_ERR_UNSUPPORTED;
 }
 
-int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
-                int w, int h, int cus, bool spread) {
-  int tw = 0, th = 0;
-  get_override(&tw, &th);
-  if (tw > 0) return plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d);
-  if (tuned_shape(dtype, fp, &tw, &th) &&
-      plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d) == MF_OK)
-    return MF_OK;
+int untuned_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
+                 int w, int h, int cus, bool spread) {
   const bool sized = w > 0 && h > 0 && cus > 0;
   ImageDesc best_gs{};
   const ImageDesc* gs = best_gs_plan(dtype, fp, lds_max, &best_gs) == MF_OK ? &best_gs : nullptr;
@@ -494,6 +488,17 @@ int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, Im
     if (sized) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
   }
   return rc;
+}
+
+int choose_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, ImageDesc* d,
+                int w, int h, int cus, bool spread) {
+  int tw = 0, th = 0;
+  get_override(&tw, &th);
+  if (tw > 0) return plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d);
+  if (tuned_shape(dtype, fp, &tw, &th) &&
+      plan_shape(dtype, fp, lds_max, imax_cap, tw, th, d) == MF_OK)
+    return MF_OK;
+  return untuned_plan(dtype, fp, lds_max, imax_cap, d, w, h, cus, spread);
 }
 
 int choose_plan_tall(int dtype, const mf_footprint* fp, int lds_max, int imax_cap,

@@ -129,3 +129,26 @@ def test_captured_after_a_larger_image(mf, dtype, r, a, b):
     del g
     torch.cuda.synchronize()
     mf.release_scratch()
+
+
+@pytest.mark.parametrize("dtype,r", [("u16", 48), ("f32", 40)])
+def test_per_thread_stream(mf, dtype, r):
+    """One handle names a stream of each host thread, so middle windows keep their
+    LDS tiles there too."""
+    import ctypes
+    img, fp = image(dtype, 2048, 2048, 1), mf.Footprint.disc(r)
+    code = {"u16": 1, "f32": 2}[dtype]
+    assert mf.query_call(2048, 2048, code, fp)["scratch_bytes"] > 0
+    exp = mf.median_filter(img, fp, "clamp")
+    out = torch.empty_like(img)
+    torch.cuda.synchronize()
+    mf.release_scratch()
+    P = ctypes.c_void_p
+    rc = mf.lib().median_filter(P(img.data_ptr()), 2048, 2048, 2048 * img.element_size(), code,
+                                fp.handle, 0, P(out.data_ptr()), P(2))   # hipStreamPerThread
+    assert rc == 0
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    mf.release_scratch()
+    assert torch.cuda.mem_get_info()[0] - free < (1 << 20)
+    assert same(out, exp)
