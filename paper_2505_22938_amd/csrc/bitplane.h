@@ -13,10 +13,10 @@
 // about 4.6 instructions per tap and plane for 32 pixels, whatever the
 // window's shape, the values or the rank; the tile engine (tile_engine.h)
 // ranks a box and walks it instead, about 2000 per pixel.  Bound by the
-// vector ALU: at 4096 x 4096 uint16, disc 5 / 8, 267 / 780 instructions per
-// pixel at 82 / 85 % of the issue rate, 1.23 -> 0.138 / 1.06 -> 0.37 ms
+// vector ALU: at 4096 x 4096 uint16, disc 5 / 8, 263 / 770 instructions per
+// pixel at 82 / 87 % of the issue rate, 1.23 -> 0.138 / 1.06 -> 0.37 ms
 // against the tile engine (uint8 disc 2 1.99 -> 0.027 ms, float32 disc 4
-// 2.07 -> 0.19 ms); the LDS is busy a third of the time.
+// 2.07 -> 0.19 ms); the LDS is busy 37 / 35 % of the time.
 //
 // The 32 pixels of a word are not neighbours: the output tile is cut into
 // GX x GY = 4 x 8 sub-tiles of SX x SY pixels and bit b of word (x, y)

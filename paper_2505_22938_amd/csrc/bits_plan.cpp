@@ -58,9 +58,10 @@ double bits_us(const Variant& v, int W, int H, int es, int lds_max, long long w,
 // The tile engine on the same image, near the line where the two paths meet:
 // what it takes at least, by the pixel (4096 x 4096, disc 8 to 16: uint8 1.21
 // ms, uint16 1.00, float32 1.35 before its first rows were halved, about 0.87
-// times that since) and for one round of the smallest tiles.  At 4096 x 4096
-// the bit planes win up to disc 11 for uint16 (0.64 ms), disc 16 for uint8
-// (0.87) and disc 10 for float32 (0.98).
+// times that since) and for one round of the smallest tiles.  At 4096 x 4096,
+// smooth content, the bit planes win up to disc 12 for uint16 (0.87 ms against
+// 0.95), disc 18 for uint8 (1.13 against 1.29) and disc 10 for float32 (0.98
+// against 1.29).
 double tile_us(int dtype, long long w, long long h) {
   const double ns = dtype == MF_U8 ? 0.063 : dtype == MF_U16 ? 0.052 : 0.072;
   return std::max(25.0, 1e-3 * ns * (double)w * (double)h);

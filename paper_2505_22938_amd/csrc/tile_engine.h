@@ -1577,7 +1577,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
       int m_l = 0, vp_l = 0, vc_l = k0, miss_l = 0;   // results, lane j = column c0 + j
       // seeds, one wave-wide solve per chunk of the round: a band's first
       // chunk from a histogram, each later chunk by moving the previous
-      // chunk's seed window 16 columns right (entering and leaving pixels
+      // chunk's seed window a chunk to the right (entering and leaving pixels
       // of every footprint row counted against its pivot, then a wave-wide
       // omnigram scan)
       for (int gg = 0; gg < 4; ++gg) {
@@ -1627,9 +1627,7 @@ __device__ __forceinline__ bool tile_body(const D& a, int tile, unsigned char* s
           miss_l = ms < 0;
         }
       }
-      // horizontal slides, all rows in lockstep; the lane's first five
-      // footprint rows' offsets stay in registers
-
+      // horizontal slides, all rows in lockstep
       const int steps = __builtin_amdgcn_readfirstlane(
           max(max(__shfl(len, 0, 64), __shfl(len, 16, 64)),
               max(__shfl(len, 32, 64), __shfl(len, 48, 64))));
