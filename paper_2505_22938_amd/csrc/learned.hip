@@ -533,11 +533,13 @@ int bracketed_filter(mf_learned* n, const uint2* br, const void* img, int w, int
   }
   const long long fntiles = (long long)f.tiles_x * f.tiles_y;
   long long fgrid = fntiles;
+  std::unique_lock<std::mutex> hold;   // until the pass that uses the scratch is queued
   if (f.gs) {
     const int occ = std::max(1, std::min(2, lp.di.lds_max / std::max(1, f.lds_bytes)));
     fgrid = std::min<long long>(fntiles, (long long)lp.di.cus * occ);
     void* scr = nullptr;
-    if ((rc = mf::get_scratch(lp.dev, s, (size_t)fgrid * (size_t)f.slot_bytes, &scr))) return rc;
+    if ((rc = mf::get_scratch(lp.dev, s, (size_t)fgrid * (size_t)f.slot_bytes, &scr, &hold)))
+      return rc;
     f.scratch = static_cast<unsigned char*>(scr);
   }
   (void)hipFuncSetAttribute((const void*)bk, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -548,6 +550,7 @@ int bracketed_filter(mf_learned* n, const uint2* br, const void* img, int w, int
                      n->tile_fail);
   hipLaunchKernelGGL(fk, dim3((unsigned)fgrid), dim3(mf::kThreads), f.lds_bytes, s, f,
                      (const int*)n->tile_fail, n->fail_px, lp.ratio);
+  if (hold.owns_lock()) hold.unlock();
   const long long pgrid = std::max(1, lp.di.cus) * 8LL;   // 8 pixels at a time per CU
   // staging buffer: the window's taps (the kernel stages windows of at most
   // kSelStage taps)

@@ -128,6 +128,7 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
   const long long ntiles = (long long)a.tiles_x * a.tiles_y;
   if (ntiles > 0x7fffffffLL) return MF_ERR_UNSUPPORTED;
   long long grid = ntiles;
+  std::unique_lock<std::mutex> hold;
   if (a.gs) {
     grid = scratch_slots(a, di);
     if (ext_scratch) {
@@ -139,7 +140,8 @@ int launch_with_plan(ImageDesc a, int dev, const DeviceInfo& di, hipStream_t str
       a.scratch = ext_scratch + kClaimBytes;
     } else {
       void* scr = nullptr;
-      const int rc = get_scratch(dev, stream, (size_t)grid * (size_t)a.slot_bytes, &scr, keep_bytes);
+      const int rc = get_scratch(dev, stream, (size_t)grid * (size_t)a.slot_bytes, &scr, &hold,
+                                 keep_bytes);
       if (rc) return rc;
       a.scratch = static_cast<unsigned char*>(scr);
     }

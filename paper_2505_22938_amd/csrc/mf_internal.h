@@ -205,9 +205,10 @@ int validate_image(const void* img, int w, int h, size_t stride_bytes, int dtype
 // space; the kClaimBytes before it hold the tile-claim words (nine used),
 // zeroed when the buffer is allocated and left zero by every launch that
 // uses them.  Outside capture the buffer is grown to keep_bytes if that is more
-// and there is memory for it.
+// and there is memory for it.  The caller keeps `hold` until its kernel is queued.
 constexpr int kClaimBytes = 256;
-int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out, size_t keep_bytes = 0);
+int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out,
+                std::unique_lock<std::mutex>* hold, size_t keep_bytes = 0);
 int release_scratch();
 
 // Tuned tile shapes, keyed by dtype and footprint.

@@ -598,8 +598,11 @@ std::vector<std::pair<int, void*>> g_retired;   // outgrown but possibly capture
 // until mf_release_scratch, since the graph refers to it), anything else
 // returns MF_ERR_UNSUPPORTED.  Outside capture a buffer that is too small is
 // replaced; if a captured graph may refer to the old one it is retired, not
-// freed.
-int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out, size_t keep_bytes) {
+// freed.  `hold` keeps the cache locked until the caller has queued the kernel
+// that uses the buffer: another host thread's call on the stream may replace it,
+// which waits for what is queued there and no more.
+int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out,
+                std::unique_lock<std::mutex>* hold, size_t keep_bytes) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) return MF_ERR_HIP;
   const bool capturing = cap != hipStreamCaptureStatusNone;
@@ -615,7 +618,7 @@ int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out, size_t ke
     *p = nullptr;
     return false;
   };
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  *hold = std::unique_lock<std::mutex>(g_scratch_mu);
   for (auto& e : g_scratch) {
     if (e.dev == dev && e.stream == stream) {
       if (e.bytes < bytes || e.asked < want) {

@@ -2,7 +2,8 @@
 sort in LDS take no scratch into a graph, so graphs captured on one warmed
 stream replay on several streams at once, beside eager calls on it and after
 mf_release_scratch; and a stream warmed by a call on a larger image can be
-captured on a smaller one whatever shapes the two fit."""
+captured on a smaller one whatever shapes the two fit.  Two host threads on one
+stream may each need its scratch grown."""
 
 import numpy as np
 import pytest
@@ -152,3 +153,44 @@ def test_per_thread_stream(mf, dtype, r):
     mf.release_scratch()
     assert torch.cuda.mem_get_info()[0] - free < (1 << 20)
     assert same(out, exp)
+
+
+def test_two_threads_on_one_stream(mf):
+    """One thread's calls use the stream's scratch while the other's make it grow
+    again and again."""
+    import threading
+    small, sfp = image("u16", 2048, 2048, 1), mf.Footprint.disc(46)
+    big = image("f32", 900, 700, 2)
+    radii = (52, 58, 64, 70, 76, 82, 90, 100)
+    bfps = [mf.Footprint.disc(r) for r in radii]
+    exp = mf.median_filter(small, sfp, "clamp")
+    bexp = [mf.median_filter(big, fp, "clamp") for fp in bfps]
+    assert mf.query_call(2048, 2048, mf.MF_U16, sfp)["path"] == "scratch"
+    s = torch.cuda.Stream()
+    outs = [torch.empty_like(small) for _ in range(40)]
+    bouts = [torch.empty_like(big) for _ in radii]
+    torch.cuda.synchronize()
+    mf.release_scratch()
+    errors = []
+
+    def run(calls):
+        try:
+            for call in calls:
+                call()
+        except Exception as e:   # noqa: BLE001
+            errors.append(e)
+
+    a = threading.Thread(target=run, args=([lambda o=o: mf.median_filter(small, sfp, "clamp", out=o,
+                                                                         stream=s) for o in outs],))
+    b = threading.Thread(target=run, args=([lambda f=f, o=o: mf.median_filter(big, f, "clamp", out=o,
+                                                                              stream=s)
+                                            for f, o in zip(bfps, bouts)],))
+    a.start()
+    b.start()
+    a.join()
+    b.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    assert all(same(o, exp) for o in outs)
+    assert all(same(o, e) for o, e in zip(bouts, bexp))
+    mf.release_scratch()
