@@ -115,6 +115,7 @@ struct ImageDesc {
   // register capacity (elements per thread) of the LDS variant
   int kt, shape, gs, imax;
   int bits;   // 0, or 1 + the bit-plane variant (tw x th then its tile)
+  int default_gs;   // choose_plan: 1 = the default shape (before fitting) takes scratch
   // bracketed tiles (learned path): per-tile [lo, hi] keys, the number of
   // in-bracket pixels region A can hold, and the list (y * w + x) and count
   // of output pixels whose median fell outside their tile's bracket
@@ -239,34 +240,46 @@ long long scratch_slots(const ImageDesc& a, const DeviceInfo& di);
 // The LDS shape of least estimated time (MF_ERR_UNSUPPORTED: no box fits).
 int lds_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, int w, int h, int cus,
              ImageDesc* d);
+// What an uncaptured call's default plan would have taken of its stream's
+// scratch where the fitted one takes none (forgotten by release_scratch).
+void note_scratch(int dev, hipStream_t stream, size_t bytes);
+bool scratch_noted(int dev, hipStream_t stream, size_t bytes);
 // The same for the plan of choose_plan(.., spread), completed by `bind`.  Scratch
 // belongs to the stream: graphs captured on one stream bake in the same buffer
 // and tile claims, and hipStreamPerThread names a stream of each thread.  So a
 // window whose default plan is an LDS one runs on that there, and the fitted
 // global-scratch plan is for calls that the stream orders.  Where scratch is not
-// to be had (a capturing stream with too little, no memory) the default plan and
-// then an LDS one are tried.  An uncaptured call leaves the stream the scratch of
-// its default plan too, which is what a captured call on a smaller image takes.
+// to be had (a capturing stream with too little, no memory) the default plan is
+// tried.  A captured call is to run wherever an uncaptured one on an image as
+// large came before it on the stream: that one leaves the scratch of its default
+// plan, or a note of it where its tiles sort in LDS (the captured call's may
+// then, too).
 template <typename Bind>
 int launch_fitted(ImageDesc a, int dtype, const mf_footprint* fp, int w, int h, int dev,
                   const DeviceInfo& di, hipStream_t stream, Bind&& bind) {
   bind(&a);
-  if (!a.gs) return launch_with_plan(a, dev, di, stream);
+  if (!a.gs && !a.default_gs) return launch_with_plan(a, dev, di, stream);
   ImageDesc d{};
   int rc = choose_plan(dtype, fp, di.lds_max, 33, &d, w, h, di.cus, false);
   if (rc) return rc;
   bind(&d);
+  const size_t need = d.gs ? (size_t)scratch_slots(d, di) * (size_t)d.slot_bytes : 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) return MF_ERR_HIP;
-  if (!d.gs && (cap != hipStreamCaptureStatusNone || stream == hipStreamPerThread))
+  const bool known = hipStreamIsCapturing(stream, &cap) == hipSuccess;
+  const bool capturing = cap != hipStreamCaptureStatusNone;
+  if (!a.gs) {
+    if (!known) (void)hipGetLastError();
+    else if (!capturing) note_scratch(dev, stream, need);
+    return launch_with_plan(a, dev, di, stream);
+  }
+  if (!known) return MF_ERR_HIP;
+  if (!d.gs && (capturing || stream == hipStreamPerThread))
     return launch_with_plan(d, dev, di, stream);
-  rc = launch_with_plan(a, dev, di, stream, nullptr, 0,
-                        d.gs ? (size_t)scratch_slots(d, di) * (size_t)d.slot_bytes : 0);
+  rc = launch_with_plan(a, dev, di, stream, nullptr, 0, need);
   if (rc != MF_ERR_UNSUPPORTED && rc != MF_ERR_NOMEM) return rc;
   (void)hipGetLastError();
   rc = launch_with_plan(d, dev, di, stream);
-  if (rc != MF_ERR_UNSUPPORTED && rc != MF_ERR_NOMEM) return rc;
-  (void)hipGetLastError();
+  if (rc != MF_ERR_UNSUPPORTED || !scratch_noted(dev, stream, need)) return rc;
   ImageDesc l{};
   if (lds_plan(dtype, fp, di.lds_max, 33, w, h, di.cus, &l) != MF_OK) return rc;
   bind(&l);

@@ -484,8 +484,10 @@ int untuned_plan(int dtype, const mf_footprint* fp, int lds_max, int imax_cap, I
   const int rc = default_plan(dtype, fp, lds_max, imax_cap, default_th_cap(fp), w, h,
                               sized ? 4LL * cus : 0, gs, d);
   if (rc == MF_OK && spread) {
+    const int default_gs = d->gs;
     fit_plan(dtype, fp, lds_max, imax_cap, w, h, cus, gs, d);
     if (sized) spread_plan(dtype, fp, lds_max, imax_cap, w, h, cus, d);
+    d->default_gs = default_gs;
   }
   return rc;
 }
@@ -587,6 +589,7 @@ struct ScratchEntry {
   size_t bytes;
   bool captured;   // a graph captured on the stream may still use ptr
   size_t asked;    // largest size an allocation was tried for
+  size_t noted;    // largest size noted instead of allocated
 };
 std::mutex g_scratch_mu;
 std::vector<ScratchEntry> g_scratch;
@@ -646,9 +649,26 @@ int get_scratch(int dev, hipStream_t stream, size_t bytes, void** out,
     (void)hipFree(p);
     return MF_ERR_HIP;
   }
-  g_scratch.push_back({dev, stream, p, want, false, asked});
+  g_scratch.push_back({dev, stream, p, want, false, asked, 0});
   *out = static_cast<unsigned char*>(p) + kClaimBytes;
   return MF_OK;
+}
+
+void note_scratch(int dev, hipStream_t stream, size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  for (auto& e : g_scratch)
+    if (e.dev == dev && e.stream == stream) {
+      e.noted = std::max(e.noted, bytes);
+      return;
+    }
+  g_scratch.push_back({dev, stream, nullptr, 0, false, 0, bytes});
+}
+
+bool scratch_noted(int dev, hipStream_t stream, size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  for (const auto& e : g_scratch)
+    if (e.dev == dev && e.stream == stream) return e.noted >= bytes;
+  return false;
 }
 
 long long scratch_slots(const ImageDesc& a, const DeviceInfo& di) {

@@ -107,7 +107,8 @@ def test_graphs_of_one_stream_at_once(mf, dtype, r, kind):
                                          ("u16", 64, (1500, 1200), (641, 479)),
                                          ("f32", 64, (1200, 900), (800, 800)),
                                          ("f32", 100, (641, 479), (400, 300)),
-                                         ("f32", 48, (3840, 2160), (500, 301))])
+                                         ("f32", 48, (3840, 2160), (500, 301)),
+                                         ("u8", 68, (558, 624), (458, 609))])
 def test_captured_after_a_larger_image(mf, dtype, r, a, b):
     mf.release_scratch()
     fp = mf.Footprint.disc(r)
@@ -153,6 +154,28 @@ def test_per_thread_stream(mf, dtype, r):
     mf.release_scratch()
     assert torch.cuda.mem_get_info()[0] - free < (1 << 20)
     assert same(out, exp)
+
+
+def test_captured_without_an_earlier_call_is_refused(mf):
+    """Global-scratch windows on a stream that no call has used, or whose scratch
+    was released."""
+    img, fp = image("u16", 2048, 2048, 1), mf.Footprint.disc(64)
+    mf.median_filter(img, fp, "clamp")   # the table
+    out = torch.empty_like(img)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        mf.median_filter(img, fp, "clamp")
+    torch.cuda.synchronize()
+    mf.release_scratch()
+    status = None
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        out.copy_(img)
+        try:
+            mf.median_filter(img, fp, "clamp", out=out)
+        except mf.MedianFilterError as e:
+            status = e.status
+    assert status == -3
 
 
 def test_two_threads_on_one_stream(mf):
