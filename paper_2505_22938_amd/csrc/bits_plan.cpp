@@ -82,14 +82,15 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
   const int H = (int)fp->row_lo.size(), W = (int)fp->col_lo.size(), es = elem_size(dtype);
   if (H > 64) return MF_ERR_UNSUPPORTED;   // the tap table is built by one wave, a row per lane
   // the filter's limit on windows is the tile engine's, whichever path runs:
-  // the window's width and height in the smallest tile's box
-  ImageDesc smallest{};
-  if (make_plan_gs(dtype, fp, lds_max, 8, 8, &smallest) != MF_OK) return MF_ERR_UNSUPPORTED;
+  // the smallest tile's box, 8 x 8 pixels grown by the window, is at most 255
+  // wide (and 256 tall, which 64 rows are)
+  if (W + 7 > 255) return MF_ERR_UNSUPPORTED;
   int pairs = 0;
   for (int i = 0; i < H; ++i) {
     if (fp->row_hi[i] < fp->row_lo[i]) return MF_ERR_UNSUPPORTED;
     pairs += (fp->row_hi[i] - fp->row_lo[i] + 2) / 2;
   }
+  const bool huge = ((double)w + 128.0) * ((double)h + 64.0) > 4e9;   // (tiles are at most 128 x 64)
   int best = -1;
   double best_us = 1e30;
   for (int i = 0; i < kBitsVariants; ++i) {
@@ -98,8 +99,8 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
     if (v.g * v.p < pairs || lds_bytes(v, W, H, es) > lds_max) continue;
     // a launch holds fewer than 2^32 threads (half a thread to a pixel for 16
     // lanes a window; the tiles of the tile engine take a quarter)
-    const long long tiles = (long long)((w + v.tw - 1) / v.tw) * ((h + v.th - 1) / v.th);
-    if (tiles * v.threads > 0xffffffffLL) continue;
+    if (huge && (long long)((w + v.tw - 1) / v.tw) * ((h + v.th - 1) / v.th) * v.threads > 0xffffffffLL)
+      continue;
     const double t = bits_us(v, W, H, es, lds_max, w, h);
     if (t < best_us) {
       best = i;
@@ -152,7 +153,8 @@ int bits_plan(int dtype, const mf_footprint* fp, int lds_max, int w, int h, int 
 }
 
 int call_plan(int dtype, const mf_footprint* fp, const DeviceInfo& di, int w, int h, ImageDesc* d) {
-  ImageDesc t{};
+  ImageDesc t;
+  t.tw = 0;   // (set with the rest of it if tiles are the faster)
   if (bits_plan(dtype, fp, di.lds_max, w, h, di.cus, d, nullptr, &t) == MF_OK) return MF_OK;
   if (t.tw) {
     *d = t;
